@@ -75,8 +75,10 @@ enum { NPM_INIT_NORMAL = 0, NPM_INIT_UNIFORM = 1 };
  * cell (a counting sort on the device, kept in context scratch) so that a
  * wave's consecutive tiles touch nearby grid entries; NPM_ORDER_NONE keeps
  * the caller's order; NPM_ORDER_AUTO sorts training batches of 2^15
- * vertices or more, and queries of that size on grids with hashed levels
- * (on a small dense grid the gathers already hit the cache).
+ * vertices or more, and no queries: on a grid with hashed levels a query of
+ * more than 16,384 vertices (24,576 in FP32) encodes its batch level by
+ * level into context scratch first (4 bytes per vertex and grid feature, 2
+ * in the precision form), and a small dense grid stays in the caches.
  * A query's outputs do not depend on the order (each vertex keeps its own
  * uniforms; the outputs are staged and un-permuted); a gradient changes only
  * in the order of its floating-point sums.                                  */

@@ -94,8 +94,10 @@ __device__ __forceinline__ void philox_uniforms(uint64_t vertex, uint64_t seed, 
     uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        const uint32_t hi0 = __umulhi(0xD2511F53u, c0), lo0 = 0xD2511F53u * c0;
-        const uint32_t hi1 = __umulhi(0xCD9E8D57u, c2), lo1 = 0xCD9E8D57u * c2;
+        // one 64-bit product each (the 32-bit halves apart cost two)
+        const uint64_t m0 = (uint64_t)0xD2511F53u * c0, m1 = (uint64_t)0xCD9E8D57u * c2;
+        const uint32_t hi0 = (uint32_t)(m0 >> 32), lo0 = (uint32_t)m0;
+        const uint32_t hi1 = (uint32_t)(m1 >> 32), lo1 = (uint32_t)m1;
         const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
         c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
         k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
@@ -362,8 +364,14 @@ __device__ __forceinline__ void sh_bands4(float x, float y, float z, float *o)
     o[15] = 0.59004358992664352f * x * (xx - 3.0f * yy);
 }
 
-// Wave-wide helpers for the two half-waves of a tile.
-__device__ __forceinline__ float xor32(float v) { return __shfl_xor(v, 32, 64); }
+// Lane l ^ 32's value: one vector instruction swaps the two half-waves of a
+// pair of registers, with no LDS round trip.
+__device__ __forceinline__ float xor32(float v)
+{
+    // r[0]: both halves hold lanes 0..31's values, r[1]: lanes 32..63's
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
+}
 
 // ------------------------------------------------------------------ selection
 // Selection term of one sample (the learned selection probability): the

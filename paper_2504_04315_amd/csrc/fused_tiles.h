@@ -151,24 +151,29 @@ struct TileGather {
     float fr[NLV][3];
 };
 
-template <int IN_G, int F, bool BF>
-__device__ __forceinline__ void encode_issue(const GridView &gv, int h, float px, float py,
+struct LevelRef {
+    int D;
+    uint32_t off;
+    bool hashed;
+};
+// level(q): register group q's level of this half-wave
+template <int IN_G, int F, bool BF, typename LV>
+__device__ __forceinline__ void encode_issue(const GridView &gv, LV &&level, float px, float py,
                                              float pz, TileGather<IN_G, F, BF> &g)
 {
     using TG = TileGather<IN_G, F, BF>;
     using RT = typename CornerRaw<F, BF>::T;
 #pragma unroll
     for (int q = 0; q < TG::NLV; ++q) {
-        const int l = (8 * (q / TG::PER) + 4 * h) / F + q % TG::PER;
-        const int lc = l < gv.n_levels ? l : 0;      // a missing level reads level 0 (weight 0)
-        const int D = gv.res[lc];
+        const LevelRef lr = level(q);
+        const int D = lr.D;
         int cx, cy, cz;
         lattice_cell(px, D, cx, g.fr[q][0]);
         lattice_cell(py, D, cy, g.fr[q][1]);
         lattice_cell(pz, D, cz, g.fr[q][2]);
         const uint32_t d1 = (uint32_t)D + 1u;
-        const bool hashed = (gv.hashed_mask >> lc) & 1u;
-        const uint32_t off = gv.off[lc];
+        const bool hashed = lr.hashed;
+        const uint32_t off = lr.off;
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
             const uint32_t X = cx + (b & 1), Y = cy + ((b >> 1) & 1), Z = cz + ((b >> 2) & 1);
@@ -178,6 +183,20 @@ __device__ __forceinline__ void encode_issue(const GridView &gv, int h, float px
             else g.raw[q][b] = *reinterpret_cast<const RT *>(gv.g32 + (size_t)e * F);
         }
     }
+}
+
+// The same with the levels of half-wave h from the block's staged tables; a
+// level the grid does not have reads level 0 (weight 0).
+template <int IN_G, int F, bool BF>
+__device__ __forceinline__ void encode_issue(const GridView &gv, int h, float px, float py,
+                                             float pz, TileGather<IN_G, F, BF> &g)
+{
+    using TG = TileGather<IN_G, F, BF>;
+    encode_issue<IN_G, F, BF>(gv, [&](int q) {
+        const int l = (8 * (q / TG::PER) + 4 * h) / F + q % TG::PER;
+        const int lc = l < gv.n_levels ? l : 0;
+        return LevelRef{gv.res[lc], gv.off[lc], (bool)((gv.hashed_mask >> lc) & 1u)};
+    }, px, py, pz, g);
 }
 
 template <int IN_P, int IN_G, int F, bool BF>
@@ -381,39 +400,16 @@ template <> struct ProductShape<2> { static constexpr int GF = 4, SHD = 2; };
 constexpr int kStageFloats = 40;
 constexpr int kStagePdf = 16, kStageSdir = 17, kStageSpdf = 36, kStageSel = 37;
 
-// One 32-vertex tile t of a query: encode, MLP, mappings, pdf at dir, one
-// sample per vertex and its pdf.  img: the forward weight image in LDS.
-template <int IN_P, int HID_P, int NH, int F, bool BF, int PG = 0, bool SEL = false>
-__device__ __forceinline__ void query_tile(const GridView &gv, const void *img, const QueryIO &io,
-                                           int64_t t, int lane)
+// A query's tile from its raw outputs o (and the selection logit cp) on:
+// mappings, pdf at the direction (wx, wy, wz), one sample per vertex and its
+// pdf; vv the lane's vertex, st its staged slot or null.
+template <bool SEL>
+__device__ __forceinline__ void query_head(const QueryIO &io, int64_t vv, bool valid, float *st,
+                                           int lane, const float *o, float cp, float wx, float wy,
+                                           float wz)
 {
     const int h = lane >> 5;
     const int64_t n = io.n;
-    const int64_t v = t * 32 + (lane & 31);   // visiting slot
-    const bool valid = v < n;
-    // the vertex: its inputs, its uniforms and (unstaged) its outputs
-    const int64_t vv = io.perm ? (int64_t)io.perm[valid ? v : n - 1] : (valid ? v : n - 1);
-    float *st = io.stage ? io.stage + (size_t)(valid ? v : n - 1) * kStageFloats : nullptr;
-    float px, py, pz, wx = 0.0f, wy = 0.0f, wz = 0.0f;
-    if (io.rec) {
-        const f32x4 *r = reinterpret_cast<const f32x4 *>(io.rec + (size_t)(valid ? v : n - 1) * io.rec_stride);
-        const f32x4 a = r[0], b = r[1];
-        px = a[0]; py = a[1]; pz = a[2]; wx = a[3]; wy = b[0]; wz = b[1];
-    } else {
-        px = io.pos[vv]; py = io.pos[n + vv]; pz = io.pos[2 * n + vv];
-        if (io.pdf) { wx = io.dir[vv]; wy = io.dir[n + vv]; wz = io.dir[2 * n + vv]; }
-    }
-    float x[IN_P / 2];
-    // two levels' corners in flight at F = 2: the query kernel runs three
-    // waves per SIMD, which hide the rest
-    encode_tile<IN_P, F, BF, 4, (PG > 0 ? ProductShape<PG>::GF : IN_P)>(gv, h, px, py, pz, x);
-    if constexpr (PG > 0) {
-        float a7[7];
-        load_aux(io.rec, io.rec_stride, io.aux, n, valid ? v : n - 1, vv, a7);
-        aux_fill<IN_P, ProductShape<PG>::GF, ProductShape<PG>::SHD>(h, a7, x);
-    }
-    float o[16], cp = 0.0f;
-    mlp_forward<IN_P, HID_P, NH, BF, false, SEL>(img, x, nullptr, o, lane, io.wsel, &cp);
     if constexpr (SEL) {
         if (io.sel && valid && h == 0) {
             const float c = sigmoidf(cp);
@@ -424,15 +420,15 @@ __device__ __forceinline__ void query_tile(const GridView &gv, const void *img, 
     Lobe L[4];
     map_half(o, L);
     if (io.lobes && valid) {
+        float *lb = io.lobes + vv + (int64_t)h * n;       // lobe h; lobe 2 r + h is 2 r n further on
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int k = 2 * r + h;
             const f32x4 c = {L[r].theta, L[r].phi, L[r].kappa, expf(L[r].loglam)};
             if (st) {
                 *reinterpret_cast<f32x4 *>(st + 20 * h + 4 * r) = c;
             } else {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) io.lobes[(int64_t)(q * kLobes + k) * n + vv] = c[q];
+                for (int q = 0; q < 4; ++q) lb[(int64_t)(q * kLobes + 2 * r) * n] = c[q];
             }
         }
     }
@@ -488,6 +484,85 @@ __device__ __forceinline__ void query_tile(const GridView &gv, const void *img, 
     } else if (st && valid && h == 0 && io.pdf) {
         st[kStagePdf] = pdf_v;
     }
+}
+
+// Grid features of a tile vertex read from a level-major encoded batch
+// (k_encode.hip) instead of gathered: the words as stored (FP32 features, or
+// pairs of BF16 ones), kept so that a next tile's can be in flight.
+template <int IN_G, bool BF> struct FeatWords {
+    static constexpr int REGS = 4 * ((IN_G + 7) / 8);      // feature registers of a half-wave
+    static constexpr int N = BF ? REGS / 2 : REGS;
+    uint32_t w[N];
+};
+
+// gf: the grid features there are (registers past them read nothing and are 0)
+template <int IN_G, bool BF>
+__device__ __forceinline__ void feat_load(const void *feat, int gf, int64_t n, int64_t v, int h,
+                                          FeatWords<IN_G, BF> &f)
+{
+    // the half-wave's first row; the rows from it on are the same for both
+    // halves, so that their offsets stay scalar
+    constexpr int W = BF ? 2 : 1;                          // features per word
+    const uint32_t *p = reinterpret_cast<const uint32_t *>(feat) + v + (int64_t)h * (4 / W) * n;
+#pragma unroll
+    for (int i = 0; i < FeatWords<IN_G, BF>::N; ++i) {
+        const int k = nf(0, W * i);                        // half 0's first feature of the word
+        f.w[i] = k + 4 * h < gf ? p[(int64_t)(k / W) * n] : 0u;
+    }
+}
+
+template <int IN_P, int IN_G, bool BF>
+__device__ __forceinline__ void feat_take(const FeatWords<IN_G, BF> &f, int gf, int h, float *x)
+{
+    using FW = FeatWords<IN_G, BF>;
+#pragma unroll
+    for (int i = 0; i < FW::N; ++i) {
+        if constexpr (BF) {
+            x[2 * i] = __uint_as_float(f.w[i] << 16);
+            // an odd number of grid features leaves a word's upper half unwritten
+            x[2 * i + 1] = nf(h, 2 * i + 1) < gf ? __uint_as_float(f.w[i] & 0xffff0000u) : 0.0f;
+        } else {
+            x[i] = __uint_as_float(f.w[i]);
+        }
+    }
+#pragma unroll
+    for (int a = FW::REGS; a < IN_P / 2; ++a) x[a] = 0.0f;
+}
+
+// One 32-vertex tile t of a query: encode, MLP, mappings, pdf at dir, one
+// sample per vertex and its pdf.  img: the forward weight image in LDS.
+template <int IN_P, int HID_P, int NH, int F, bool BF, int PG = 0, bool SEL = false>
+__device__ __forceinline__ void query_tile(const GridView &gv, const void *img, const QueryIO &io,
+                                           int64_t t, int lane)
+{
+    const int h = lane >> 5;
+    const int64_t n = io.n;
+    const int64_t v = t * 32 + (lane & 31);   // visiting slot
+    const bool valid = v < n;
+    // the vertex: its inputs, its uniforms and (unstaged) its outputs
+    const int64_t vv = io.perm ? (int64_t)io.perm[valid ? v : n - 1] : (valid ? v : n - 1);
+    float *st = io.stage ? io.stage + (size_t)(valid ? v : n - 1) * kStageFloats : nullptr;
+    float px, py, pz, wx = 0.0f, wy = 0.0f, wz = 0.0f;
+    if (io.rec) {
+        const f32x4 *r = reinterpret_cast<const f32x4 *>(io.rec + (size_t)(valid ? v : n - 1) * io.rec_stride);
+        const f32x4 a = r[0], b = r[1];
+        px = a[0]; py = a[1]; pz = a[2]; wx = a[3]; wy = b[0]; wz = b[1];
+    } else {
+        px = io.pos[vv]; py = io.pos[n + vv]; pz = io.pos[2 * n + vv];
+        if (io.pdf) { wx = io.dir[vv]; wy = io.dir[n + vv]; wz = io.dir[2 * n + vv]; }
+    }
+    float x[IN_P / 2];
+    // two levels' corners in flight at F = 2: the query kernel runs three
+    // waves per SIMD, which hide the rest
+    encode_tile<IN_P, F, BF, 4, (PG > 0 ? ProductShape<PG>::GF : IN_P)>(gv, h, px, py, pz, x);
+    if constexpr (PG > 0) {
+        float a7[7];
+        load_aux(io.rec, io.rec_stride, io.aux, n, valid ? v : n - 1, vv, a7);
+        aux_fill<IN_P, ProductShape<PG>::GF, ProductShape<PG>::SHD>(h, a7, x);
+    }
+    float o[16], cp = 0.0f;
+    mlp_forward<IN_P, HID_P, NH, BF, false, SEL>(img, x, nullptr, o, lane, io.wsel, &cp);
+    query_head<SEL>(io, vv, valid, st, lane, o, cp, wx, wy, wz);
 }
 
 // Stages a session's grid level table into LDS.

@@ -25,81 +25,9 @@
 // accumulation; mappings, softmax, log-density and sampling in FP32.
 #include <type_traits>
 
-#include "fused_tiles.h"
+#include "fused_launch.h"
 
 namespace npm {
-
-struct FusedArgs {
-    GridDesc g;
-    int64_t n;
-    const float *pos, *dir, *rad, *spdf;
-    const float *grid32;     // FP32 grid (plain form)
-    const __half *grid16;    // FP16 grid (precision form)
-    const void *img;         // packed MLP images: forward then backward
-    int fwd_elems, bwd_elems;
-    int n_in, width;
-    uint64_t seed;
-    uint32_t sid;
-    float *lobes, *pdf, *sdir, *spdf_out;
-    float *grad;             // accumulated gradient (backward)
-    float *dw_part;          // per-wave weight-gradient partials (backward)
-    double *partials;        // per-block FP64 loss partials
-    float invN;
-    const uint32_t *perm;    // visiting order of the vertices (backward), or null
-    float *dg_tiles;         // per-tile dG for the aggregated scatter (backward)
-    float *qstage;           // staged query outputs in visiting order (with perm)
-    const float *rec;        // inputs in visiting order (with perm), rec_stride floats each
-    const float *aux;        // NPM-product inputs [7][n]
-    int rec_stride;
-    // learned selection probability (networks with the selection output)
-    const float *wsel;       // the selection row of the last layer (FP32 weights)
-    const float *bsdf;       // BSDF densities [n] of the selection term (backward), or null
-    double *partials_sel;    // per-block FP64 partials of the selection loss
-    float *sel;              // selection probability [n] (query), or null
-};
-// SEL: the network has the selection output (its logit is computed from the
-// last hidden layer and the row staged in LDS; a.sel receives sigmoid of it).
-template <int IN_P, int HID_P, int NH, int F, bool BF, int PG, bool SEL = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_query_fused(FusedArgs a)
-{
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    __shared__ uint32_t s_off[NPM_MAX_LEVELS];
-    __shared__ int s_res[NPM_MAX_LEVELS];
-    __shared__ __attribute__((aligned(16))) float s_wsel[SEL ? HID_P : 4];
-    {
-        const int bytes = a.fwd_elems * (BF ? 2 : 4);
-        for (int i = threadIdx.x; i < bytes / 16; i += blockDim.x)
-            reinterpret_cast<f32x4 *>(smem)[i] = reinterpret_cast<const f32x4 *>(a.img)[i];
-        stage_levels(a.g, s_off, s_res);
-        if constexpr (SEL)
-            for (int i = threadIdx.x; i < HID_P; i += blockDim.x)
-                s_wsel[i] = i < a.width ? a.wsel[i] : 0.0f;
-    }
-    __syncthreads();
-    const GridView gv = grid_view(a.g, s_off, s_res, a.grid32, a.grid16);
-    const QueryIO io{a.n, a.pos, a.dir, a.lobes, a.pdf, a.sdir, a.spdf_out, a.seed, a.sid,
-                     a.perm, a.qstage, a.rec, a.aux, a.rec_stride, a.sel, s_wsel};
-    const int lane = threadIdx.x & 63;
-    const int64_t ntiles = (a.n + 31) / 32;
-    const int wpb = blockDim.x / 64, wave = threadIdx.x >> 6;
-    if (gridDim.x % 8 == 0) {
-        // Workgroups are dispatched to the eight XCDs in turn (block b on XCD
-        // b mod 8), each XCD with its own L2: give each XCD a contiguous
-        // eighth of the tiles, so that the tiles it runs at one time are
-        // neighbours in the batch's order and share grid lines in its L2
-        // (FP32 query 0.56 -> 0.53 ms at 2^20 vertices).  Any placement of
-        // the blocks still covers every tile once.
-        const int64_t xcd = blockIdx.x % 8, bl = blockIdx.x / 8;
-        const int64_t wpx = (int64_t)(gridDim.x / 8) * wpb, span = (ntiles + 7) / 8;
-        const int64_t t0 = xcd * span, t1 = t0 + span < ntiles ? t0 + span : ntiles;
-        for (int64_t t = t0 + bl * wpb + wave; t < t1; t += wpx)
-            query_tile<IN_P, HID_P, NH, F, BF, PG, SEL>(gv, smem, io, t, lane);
-    } else {
-        const int64_t nwaves = (int64_t)gridDim.x * wpb;
-        for (int64_t t = blockIdx.x * (int64_t)wpb + wave; t < ntiles; t += nwaves)
-            query_tile<IN_P, HID_P, NH, F, BF, PG, SEL>(gv, smem, io, t, lane);
-    }
-}
 
 // ------------------------------------------------------------------ training
 // The block-cooperative weight gradients (BlockPlan, dw_phase, dw_write) are
@@ -445,37 +373,6 @@ __global__ __launch_bounds__(256) void k_scatter_tiles(GridDesc g, int64_t n,
     }
 }
 
-// Moves the staged outputs of a spatially ordered query to the caller's SoA
-// buffers: vertex i (coalesced writes) reads its 160-byte slot inv[i].
-__global__ __launch_bounds__(256) void k_query_unstage(int64_t n, const uint32_t *__restrict__ inv,
-                                                       const float *__restrict__ stage,
-                                                       float *__restrict__ lobes,
-                                                       float *__restrict__ pdf,
-                                                       float *__restrict__ sdir,
-                                                       float *__restrict__ spdf,
-                                                       float *__restrict__ sel)
-{
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const f32x4 *src = reinterpret_cast<const f32x4 *>(stage + (size_t)inv[i] * kStageFloats);
-    f32x4 r[kStageFloats / 4];
-#pragma unroll
-    for (int q = 0; q < kStageFloats / 4; ++q) r[q] = src[q];
-    const float *c = reinterpret_cast<const float *>(r);
-    if (lobes)
-#pragma unroll
-        for (int k = 0; k < kLobes; ++k)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                lobes[(int64_t)(q * kLobes + k) * n + i] = c[20 * (k & 1) + 4 * (k >> 1) + q];
-    if (pdf) pdf[i] = c[kStagePdf];
-    if (sdir)
-#pragma unroll
-        for (int d = 0; d < 3; ++d) sdir[(int64_t)d * n + i] = c[kStageSdir + d];
-    if (spdf) spdf[i] = c[kStageSpdf];
-    if (sel) sel[i] = c[kStageSel];
-}
-
 // Sum of the blocks' weight-gradient partials into the gradient: a block of
 // 256 threads covers 16 weights, its 16 thread rows a sixteenth of the
 // partials each (several loads in flight per thread, 768 blocks at the
@@ -506,39 +403,6 @@ __global__ __launch_bounds__(256) void k_dw_sum(const float *__restrict__ part, 
 }
 
 // ------------------------------------------------------------------ launch
-static FusedArgs fused_args(npm_ctx *ctx, int64_t n, const float *pos)
-{
-    FusedArgs a{};
-    const Net &net = ctx->net;
-    a.g = net.grid;
-    a.n = n;
-    a.pos = pos;
-    a.grid32 = ctx->params;
-    a.grid16 = (const __half *)ctx->grid16;
-    const bool bf = net.cfg.precision == NPM_PREC_BF16;
-    a.img = bf ? ctx->mlp_img16 : (const void *)ctx->mlp_img;
-    a.fwd_elems = (int)net.mlp.fwd_elems;
-    a.bwd_elems = (int)net.mlp.bwd_elems;
-    a.n_in = net.mlp.n_in;
-    a.width = net.mlp.width;
-    a.rec_stride = net.cfg.sh_degree ? 16 : 8;
-    return a;
-}
-
-template <int IN_P, int HID_P, int NH, int F, bool BF, int PG = 0, bool SEL = false>
-static hipError_t run_query(npm_ctx *ctx, FusedArgs a, hipStream_t s)
-{
-    const int64_t tiles = (a.n + 31) / 32;
-    const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((tiles + 3) / 4, 2048));
-    const size_t lds = (size_t)a.fwd_elems * (BF ? 2 : 4);
-    auto k = k_query_fused<IN_P, HID_P, NH, F, BF, PG, SEL>;
-    const hipError_t e = hipFuncSetAttribute((const void *)k,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k, dim3(blocks), dim3(256), lds, s, a);
-    return hipGetLastError();
-}
-
 // Blocks of the training kernel: one per compute unit at most (the weight
 // image and the exchange buffer take most of its LDS), WV waves each.
 constexpr int kTrainWaves = 4;
@@ -575,77 +439,6 @@ static hipError_t run_backward(npm_ctx *ctx, FusedArgs a, hipStream_t s)
     return hipGetLastError();
 }
 
-#define NPM_FUSED_DISPATCH(RUN, BFV)                                                              \
-    do {                                                                                          \
-        const MlpDesc &m_ = ctx->net.mlp;                                                         \
-        const int F_ = ctx->net.grid.feat;                                                        \
-        const int key_ = F_ * 1000 + (m_.in_p == 32) * 100 + (m_.hid_p == 64) * 10 + m_.n_hidden; \
-        switch (key_) {                                                                           \
-        case 1002: e = RUN<16, 32, 2, 1, BFV>(ctx, a, s); break;                                  \
-        case 1112: e = RUN<32, 64, 2, 1, BFV>(ctx, a, s); break;                                  \
-        case 1113: e = RUN<32, 64, 3, 1, BFV>(ctx, a, s); break;                                  \
-        case 2002: e = RUN<16, 32, 2, 2, BFV>(ctx, a, s); break;                                  \
-        case 2012: e = RUN<16, 64, 2, 2, BFV>(ctx, a, s); break;                                  \
-        case 2112: e = RUN<32, 64, 2, 2, BFV>(ctx, a, s); break;                                  \
-        case 2113: e = RUN<32, 64, 3, 2, BFV>(ctx, a, s); break;                                  \
-        case 4012: e = RUN<16, 64, 2, 4, BFV>(ctx, a, s); break;                                  \
-        case 4013: e = RUN<16, 64, 3, 4, BFV>(ctx, a, s); break;                                  \
-        case 4112: e = RUN<32, 64, 2, 4, BFV>(ctx, a, s); break;                                  \
-        case 4113: e = RUN<32, 64, 3, 4, BFV>(ctx, a, s); break;                                  \
-        default: return hipErrorNotSupported;                                                     \
-        }                                                                                         \
-    } while (0)
-
-// NPM-product shapes (sh_degree 4 on 32 grid features, 65 inputs in a 96-wide
-// first layer; sh_degree 2 on 4 grid features, 13 inputs).
-#define NPM_FUSED_PRODUCT_DISPATCH(RUN, BFV)                                                      \
-    do {                                                                                          \
-        const MlpDesc &m_ = ctx->net.mlp;                                                         \
-        const int F_ = ctx->net.grid.feat;                                                        \
-        const int key_ = m_.sh_degree * 100000 + F_ * 10000 + m_.in_p * 100 +                    \
-                         (m_.hid_p == 64) * 10 + m_.n_hidden;                                     \
-        switch (key_) {                                                                           \
-        case 429612: e = RUN<96, 64, 2, 2, BFV, 1>(ctx, a, s); break;                             \
-        case 429613: e = RUN<96, 64, 3, 2, BFV, 1>(ctx, a, s); break;                             \
-        case 449612: e = RUN<96, 64, 2, 4, BFV, 1>(ctx, a, s); break;                             \
-        case 449613: e = RUN<96, 64, 3, 4, BFV, 1>(ctx, a, s); break;                             \
-        case 221602: e = RUN<16, 32, 2, 2, BFV, 2>(ctx, a, s); break;                             \
-        default: return hipErrorNotSupported;                                                     \
-        }                                                                                         \
-    } while (0)
-
-// Networks with the selection output: the tiny (4 inputs, width 8), cfg1
-// (16 inputs, 64 x 2), the paper's (32 inputs, 64 x 2) and the production
-// (32 inputs, 64 x 3) shapes.
-#define NPM_FUSED_SEL_DISPATCH(RUN, BFV)                                                          \
-    do {                                                                                          \
-        const MlpDesc &m_ = ctx->net.mlp;                                                         \
-        const int F_ = ctx->net.grid.feat;                                                        \
-        const int key_ = F_ * 1000 + (m_.in_p == 32) * 100 + (m_.hid_p == 64) * 10 + m_.n_hidden; \
-        switch (key_) {                                                                           \
-        case 2002: e = RUN<16, 32, 2, 2, BFV, 0, true>(ctx, a, s); break;                         \
-        case 4012: e = RUN<16, 64, 2, 4, BFV, 0, true>(ctx, a, s); break;                         \
-        case 4112: e = RUN<32, 64, 2, 4, BFV, 0, true>(ctx, a, s); break;                         \
-        case 2113: e = RUN<32, 64, 3, 2, BFV, 0, true>(ctx, a, s); break;                         \
-        default: return hipErrorNotSupported;                                                     \
-        }                                                                                         \
-    } while (0)
-
-#define NPM_FUSED_RUN(RUN)                                                                        \
-    do {                                                                                          \
-        const bool bf_ = ctx->net.cfg.precision == NPM_PREC_BF16;                                 \
-        if (ctx->net.cfg.learn_selection) {                                                       \
-            if (bf_) NPM_FUSED_SEL_DISPATCH(RUN, true);                                           \
-            else NPM_FUSED_SEL_DISPATCH(RUN, false);                                              \
-        } else if (ctx->net.mlp.sh_degree > 0) {                                                  \
-            if (bf_) NPM_FUSED_PRODUCT_DISPATCH(RUN, true);                                       \
-            else NPM_FUSED_PRODUCT_DISPATCH(RUN, false);                                          \
-        } else {                                                                                  \
-            if (bf_) NPM_FUSED_DISPATCH(RUN, true);                                               \
-            else NPM_FUSED_DISPATCH(RUN, false);                                                  \
-        }                                                                                         \
-    } while (0)
-
 bool fused_shape_supported(const Net &net)
 {
     const MlpDesc &m = net.mlp;
@@ -668,43 +461,6 @@ bool fused_shape_supported(const Net &net)
     case 4012: case 4013: case 4112: case 4113: return m.in_p <= 32;
     default: return false;
     }
-}
-
-hipError_t fused_query(npm_ctx *ctx, int64_t n, const float *pos, const float *aux,
-                       const float *dir, uint64_t seed, uint32_t stream_id, float *lobes,
-                       float *pdf, float *sdir, float *spdf, const uint32_t *perm,
-                       const uint32_t *inv, const float *rec, float *stage, hipStream_t s,
-                       float *sel)
-{
-    FusedArgs a = fused_args(ctx, n, pos);
-    a.aux = aux;
-    const Weights w = query_weights(ctx);
-    a.grid32 = w.grid32;
-    a.grid16 = (const __half *)w.grid16;
-    a.img = ctx->net.cfg.precision == NPM_PREC_BF16 ? w.img16 : (const void *)w.img;
-    a.dir = dir;
-    a.seed = seed;
-    a.sid = stream_id;
-    a.lobes = lobes;
-    a.pdf = pdf;
-    a.sdir = sdir;
-    a.spdf_out = spdf;
-    a.perm = perm;
-    a.qstage = perm ? stage : nullptr;
-    a.rec = perm ? rec : nullptr;
-    a.wsel = selection_row(ctx, w.grid32);
-    a.sel = sel;
-    hipError_t e = hipSuccess;
-    int tok;
-    timed_begin(ctx, "fused_query", s, &tok);
-    NPM_FUSED_RUN(run_query);
-    timed_end(ctx, tok, s);
-    if (e != hipSuccess || !perm) return e;
-    timed_begin(ctx, "query_unstage", s, &tok);
-    hipLaunchKernelGGL(k_query_unstage, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, inv,
-                       stage, lobes, pdf, sdir, spdf, sel);
-    timed_end(ctx, tok, s);
-    return hipGetLastError();
 }
 
 hipError_t fused_backward(npm_ctx *ctx, int64_t n, const float *pos, const float *aux,

@@ -44,45 +44,6 @@ hipError_t staged_corner_index(npm_ctx *ctx, int64_t n, const float *pos, uint32
 }
 
 // ============================================================= encode
-template <int F>
-__device__ __forceinline__ void load_feat(const float *__restrict__ grid, uint32_t e, float *v)
-{
-    if constexpr (F == 1) {
-        v[0] = grid[e];
-    } else if constexpr (F == 2) {
-        const float2 t = *reinterpret_cast<const float2 *>(grid + 2 * (size_t)e);
-        v[0] = t.x; v[1] = t.y;
-    } else {
-        const float4 t = *reinterpret_cast<const float4 *>(grid + 4 * (size_t)e);
-        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-    }
-}
-
-// One thread per (vertex, level): the level is uniform across the block.
-template <int F>
-__global__ __launch_bounds__(256) void k_encode(GridDesc g, int64_t n, const float *__restrict__ pos,
-                                                const float *__restrict__ grid,
-                                                float *__restrict__ G)
-{
-    const int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int l = blockIdx.y;
-    if (v >= n) return;
-    Corners c;
-    level_corners(g, l, pos[v], pos[n + v], pos[2 * n + v], c);
-    float acc[F];
-#pragma unroll
-    for (int f = 0; f < F; ++f) acc[f] = 0.0f;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        float val[F];
-        load_feat<F>(grid, c.e[b], val);
-#pragma unroll
-        for (int f = 0; f < F; ++f) acc[f] += c.w[b] * val[f];
-    }
-#pragma unroll
-    for (int f = 0; f < F; ++f) G[((int64_t)l * F + f) * n + v] = acc[f];
-}
-
 // NPM-product rows of the MLP input: G[gf + k][v] for the SH of omega_o
 // (d^2 values), of the normal (d^2), and the roughness; aux is [7][n].
 __global__ void k_aux_rows(int64_t n, int gf, int deg, const float *__restrict__ aux,
@@ -104,15 +65,10 @@ hipError_t staged_encode(npm_ctx *ctx, int64_t n, const float *pos, float *G, hi
 {
     const GridDesc &g = ctx->net.grid;
     const float *table = w ? w->grid32 : ctx->params;
-    dim3 grid((unsigned)((n + 255) / 256), (unsigned)g.n_levels);
     int tok;
     timed_begin(ctx, "staged_encode", s, &tok);
-    switch (g.feat) {
-    case 1: hipLaunchKernelGGL(k_encode<1>, grid, dim3(256), 0, s, g, n, pos, table, G); break;
-    case 2: hipLaunchKernelGGL(k_encode<2>, grid, dim3(256), 0, s, g, n, pos, table, G); break;
-    case 4: hipLaunchKernelGGL(k_encode<4>, grid, dim3(256), 0, s, g, n, pos, table, G); break;
-    default: return hipErrorInvalidValue;
-    }
+    const hipError_t e = launch_grid_encode(g, n, pos, nullptr, 0, table, nullptr, false, G, s);
+    if (e != hipSuccess) return e;
     if (ctx->net.mlp.sh_degree > 0)
         hipLaunchKernelGGL(k_aux_rows, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n,
                            ctx->net.mlp.gf, ctx->net.mlp.sh_degree, aux, G);

@@ -100,6 +100,9 @@ struct npm_ctx {
     float *s_rec = nullptr;            // [sort_n][8] inputs in visiting order
     float *s_qstage = nullptr;         // [qstage_n][40] staged query outputs
     int64_t qstage_n = 0;
+    // grid features of a batch encoded level by level: 32-bit words
+    uint32_t *s_feat = nullptr;
+    size_t feat_cap = 0;
     uint32_t *s_cells = nullptr;       // 2^18 cell counts / offsets, 256 block totals
     int64_t sort_n = 0;
     // per-tile dG of a fused training batch, for the aggregated scatter
@@ -170,6 +173,21 @@ hipError_t launch_reduce_partials(npm_ctx *ctx, int nparts, double *out, hipStre
 hipError_t launch_reduce_scaled(const double *part, int nparts, double scale, double *out,
                                 hipStream_t s);
 hipError_t launch_fill_f32(float *p, int64_t n, float v, hipStream_t s);
+
+// level-major grid encoding (k_encode.hip): the features of n vertices,
+// positions from pos [3][n] or (rec set) the first three floats of rec's
+// records, rec_stride floats each.  b16: from the FP16 table, rounded to BF16
+// and stored in feature pairs [ceil(features / 2)][n]; otherwise FP32
+// [features][n].
+hipError_t launch_grid_encode(const GridDesc &g, int64_t n, const float *pos, const float *rec,
+                              int rec_stride, const float *grid32, const void *grid16, bool b16,
+                              void *out, hipStream_t s);
+// 32-bit words of its output
+inline size_t feat_words(const Net &net, int64_t n)
+{
+    const int gf = net.mlp.gf;
+    return (size_t)(net.cfg.precision == NPM_PREC_BF16 ? (gf + 1) / 2 : gf) * (size_t)n;
+}
 
 // staged path (k_staged.hip)
 hipError_t staged_corner_index(npm_ctx *ctx, int64_t n, const float *pos, uint32_t *idx,
@@ -255,17 +273,37 @@ hipError_t binned_scatter(npm_ctx *ctx, const BinDesc &b, int64_t n, const float
                           const float *dgt, int rows, float *grad, uint32_t *cnt,
                           uint32_t *items, hipStream_t s);
 
-// fused path (k_fused.hip)
+// fused path (k_query.hip, k_fused.hip)
 // whether the fused kernels are instantiated for the network's shape (the
 // dispatch tables of k_fused.hip)
 bool fused_shape_supported(const Net &net);
+// Queries of at most this many vertices (a 32-vertex tile for each of the 1,024
+// SIMDs) run one wave per block with the weights in registers
+// (k_query_small); a larger batch gives a SIMD several tiles, which then share
+// one weight image in LDS.  On the 8-level dense grid, FP32, 4,096 vertices
+// 20.3 -> 16.3 us, 32,768 23.0 -> 20.9 us, and 65,536 would be 41 against 34 us.
+constexpr int64_t kQuerySmall = 1 << 15;
+// Queries of more vertices than this on a grid with hashed levels encode the
+// batch level by level first (k_encode.hip): the second launch costs 3 us,
+// and up to here gathering every corner of a tile at once is no slower.  16
+// levels, 2^19 entries, gathered / encoded first: FP32 8,192 vertices 23.1 /
+// 23.5 us, 20,011 33.0 / 38.5, 32,768 57.8 / 43.9; BF16 16,384 22.1 / 22.3,
+// 20,011 24.6 / 23.3, 32,768 48.4 / 26.6.  2^20 vertices against the spatially
+// ordered gather kernel with its sort and un-permute: FP32 711 -> 666 us,
+// BF16 588 -> 420.  A dense grid's levels stay in the caches, and its corners
+// are gathered in the query kernel at every size (8 levels, 921,600 vertices,
+// FP32 296 us against 355 encoded first).
+constexpr int64_t kFeatQuery32 = 24576, kFeatQuery16 = 16384;
+
 // perm/inv (optional): visiting order and its inverse; the outputs then go
-// through `stage` (n slots of 40 floats) and an un-permuting pass
+// through `stage` (n slots of 40 floats) and an un-permuting pass.  feat
+// (optional, without perm): a buffer of feat_words(net, n) words for the
+// batch's grid features, encoded level by level in a pass of its own
 hipError_t fused_query(npm_ctx *ctx, int64_t n, const float *pos, const float *aux,
                        const float *dir, uint64_t seed, uint32_t stream_id, float *lobes,
                        float *pdf, float *sdir, float *spdf, const uint32_t *perm,
                        const uint32_t *inv, const float *rec, float *stage, hipStream_t s,
-                       float *sel = nullptr);
+                       float *sel = nullptr, void *feat = nullptr);
 // perm (optional): the order in which to visit the vertices; dg_tiles: the
 // per-tile dG buffer (required when grad is set); bins (optional): the levels
 // to scatter through the binned pass, with the context's bin buffers

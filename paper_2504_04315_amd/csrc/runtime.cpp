@@ -317,7 +317,7 @@ static void free_ctx(npm_ctx *ctx)
                     (void *)ctx->adam_v, ctx->grid16, (void *)ctx->mlp_img, ctx->mlp_img16,
                     (void *)ctx->partials, (void *)ctx->stats, (void *)ctx->s_dw_part,
                     (void *)ctx->s_perm, (void *)ctx->s_inv, (void *)ctx->s_rec,
-                    (void *)ctx->s_qstage,
+                    (void *)ctx->s_qstage, (void *)ctx->s_feat,
                     (void *)ctx->s_cells, (void *)ctx->s_dgt, (void *)ctx->s_bin_cnt,
                     (void *)ctx->s_bin_items,
                     (void *)ctx->ema, (void *)ctx->ema_img, ctx->ema_img16, ctx->ema_grid16})
@@ -455,6 +455,8 @@ static npm_status check_aux(npm_ctx *ctx, int64_t n, const float *aux)
 static bool use_order(const npm_ctx *ctx, int64_t n, bool query = false);
 static hipError_t ensure_sort(npm_ctx *ctx, int64_t n);
 static hipError_t ensure_qstage(npm_ctx *ctx, int64_t n);
+static bool use_feat(const npm_ctx *ctx, int64_t n);
+static hipError_t ensure_feat(npm_ctx *ctx, int64_t n);
 
 npm_status npm_query(npm_ctx *ctx, int64_t n, const float *pos, const float *dir,
                      uint64_t rng_seed, uint32_t rng_stream, float *lobes, float *pdf,
@@ -475,7 +477,11 @@ static npm_status query_impl(npm_ctx *ctx, int64_t n, const float *pos, const fl
     try {
         if (ctx->net.cfg.exec_mode == NPM_EXEC_FUSED) {
             const uint32_t *perm = nullptr;
-            if (use_order(ctx, n, true) && any) {
+            void *feat = nullptr;
+            if (use_feat(ctx, n) && any) {
+                NPM_HIP(ensure_feat(ctx, n), "feature scratch allocation");
+                feat = ctx->s_feat;
+            } else if (use_order(ctx, n, true) && any) {
                 NPM_HIP(ensure_sort(ctx, n), "order scratch allocation");
                 NPM_HIP(ensure_qstage(ctx, n), "query staging allocation");
                 NPM_HIP(spatial_order(ctx, n, pos, aux, dir, nullptr, nullptr, ctx->s_perm,
@@ -484,7 +490,7 @@ static npm_status query_impl(npm_ctx *ctx, int64_t n, const float *pos, const fl
             }
             NPM_HIP(fused_query(ctx, n, pos, aux, dir, rng_seed, rng_stream, lobes, pdf,
                                 sample_dir, sample_pdf, perm, ctx->s_inv, ctx->s_rec,
-                                ctx->s_qstage, s, sel), "fused query");
+                                ctx->s_qstage, s, sel, feat), "fused query");
             return NPM_OK;
         }
         NPM_HIP(ensure_scratch(ctx, n), "scratch allocation");
@@ -530,17 +536,37 @@ static npm_status check_train(npm_ctx *ctx, int64_t n, const float *pos, const f
 }
 
 // Whether a fused call visits a batch of n vertices in spatial order.  Auto
-// sorts training batches of kSortMinBatch or more, and queries of that size
-// on grids with hashed levels: on the paper's dense 8-level grid (16.5 MB)
-// an unordered 921,600-vertex query takes 0.32 ms and an ordered one 0.44 ms
-// with the sort and the un-permute, while on the 16-level hash grid ordering
-// saves a fifth of the query.
+// sorts training batches of kSortMinBatch or more, and no queries (see
+// use_feat).
 static bool use_order(const npm_ctx *ctx, int64_t n, bool query)
 {
     const int order = ctx->net.cfg.batch_order;
-    const bool auto_sorts = n >= kSortMinBatch && (!query || ctx->net.grid.hashed_mask != 0);
     return ctx->net.cfg.exec_mode == NPM_EXEC_FUSED && n > 1 &&
-           (order == NPM_ORDER_SPATIAL || (order == NPM_ORDER_AUTO && auto_sorts));
+           (order == NPM_ORDER_SPATIAL ||
+            (order == NPM_ORDER_AUTO && !query && n >= kSortMinBatch));
+}
+
+// Whether a query encodes its batch level by level first (k_encode.hip).
+static bool use_feat(const npm_ctx *ctx, int64_t n)
+{
+    const bool bf = ctx->net.cfg.precision == NPM_PREC_BF16;
+    return ctx->net.cfg.batch_order == NPM_ORDER_AUTO && ctx->net.grid.hashed_mask != 0 &&
+           n > (bf ? kFeatQuery16 : kFeatQuery32);
+}
+
+static hipError_t ensure_feat(npm_ctx *ctx, int64_t n)
+{
+    const size_t words = feat_words(ctx->net, n);
+    if (words <= ctx->feat_cap) return hipSuccess;
+    hipError_t e = hipDeviceSynchronize();
+    if (e != hipSuccess) return e;
+    if (ctx->s_feat) (void)hipFree(ctx->s_feat);
+    ctx->s_feat = nullptr;
+    ctx->feat_cap = 0;
+    e = hipMalloc((void **)&ctx->s_feat, words * 4);
+    if (e != hipSuccess) return e;
+    ctx->feat_cap = words;
+    return hipSuccess;
 }
 
 // The binned pass of a fused training batch: the plan, or false for the
