@@ -34,6 +34,8 @@ struct FusedArgs {
     double *partials_sel;    // per-block FP64 partials of the selection loss
     float *sel;              // selection probability [n] (query), or null
     const void *feat;        // level-major grid features of the batch (k_encode.hip)
+    const __bf16 *img_t;     // packed BF16 image of W^T (the backward image), and the two
+    const __bf16 *img_split; // further planes of its three-way split (FP32 training)
 };
 
 inline FusedArgs fused_args(npm_ctx *ctx, int64_t n, const float *pos)
@@ -125,5 +127,24 @@ inline FusedArgs fused_args(npm_ctx *ctx, int64_t n, const float *pos)
             else NPM_FUSED_DISPATCH(RUN, false);                                                  \
         }                                                                                         \
     } while (0)
+
+// Blocks of the training kernels: one per compute unit at most (the weight
+// images take most of its LDS), four waves each.
+constexpr int kTrainWaves = 4;
+constexpr int kTrainMaxBlocks = 256;
+inline int train_blocks(int64_t n)
+{
+    const int64_t tiles = (n + 31) / 32;
+    return (int)std::max<int64_t>(1, std::min<int64_t>((tiles + kTrainWaves - 1) / kTrainWaves,
+                                                       kTrainMaxBlocks));
+}
+
+// Dynamic LDS a training block may take: gfx950's 160 KB per workgroup less
+// room for the kernel's static arrays (level table, FP64 loss partials).
+constexpr size_t kLdsBytes = 160 * 1024 - 4096;
+
+// The training tile kernel of a batch with encoded features (k_train.hip);
+// args as for the gathering kernel, feat set.
+hipError_t train_tile(npm_ctx *ctx, const FusedArgs &args, hipStream_t s);
 
 }  // namespace npm

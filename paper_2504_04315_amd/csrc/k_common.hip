@@ -111,41 +111,35 @@ struct PackDesc {
     int64_t total;
 };
 
+// The weight that element idx of the packed image (FP32 or BF16 order) holds.
 template <bool BF16>
-__global__ void k_pack(PackDesc d, const float *__restrict__ params, float *__restrict__ img32,
-                       __bf16 *__restrict__ img16)
+__device__ __forceinline__ float pack_value(const PackDesc &d, int64_t i, const float *__restrict__ params)
 {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < d.total;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        int si = 0;
-        while (si + 1 < d.n_seg && i >= d.seg[si + 1].dst) ++si;
-        const PackSeg &g = d.seg[si];
-        const int64_t k = i - g.dst;
-        int lane, b, step;
-        if (!BF16) {
-            const int e = (int)(k & 3);
-            lane = (int)((k >> 2) & 63);
-            const int64_t rest = k >> 8;
-            const int ns4 = g.in_p / 8;
-            b = (int)(rest / ns4);
-            step = (int)(rest % ns4) * 4 + e;
-        } else {
-            const int e = (int)(k & 7);
-            lane = (int)((k >> 3) & 63);
-            const int64_t rest = k >> 9;
-            const int ns = g.in_p / 16;
-            b = (int)(rest / ns);
-            step = (int)(rest % ns) * 8 + e;
-        }
-        const int row = 32 * b + (lane & 31);
-        const int col = nf(lane >> 5, step);
-        float v = 0.0f;
-        if (row < g.out_r && col < g.in_r)
-            v = g.transpose ? params[g.src + (int64_t)col * g.ld + row]
-                            : params[g.src + (int64_t)row * g.ld + col];
-        if (BF16) img16[i] = (__bf16)v;
-        else img32[i] = v;
+    int si = 0;
+    while (si + 1 < d.n_seg && i >= d.seg[si + 1].dst) ++si;
+    const PackSeg &g = d.seg[si];
+    const int64_t k = i - g.dst;
+    int lane, b, step;
+    if (!BF16) {
+        const int e = (int)(k & 3);
+        lane = (int)((k >> 2) & 63);
+        const int64_t rest = k >> 8;
+        const int ns4 = g.in_p / 8;
+        b = (int)(rest / ns4);
+        step = (int)(rest % ns4) * 4 + e;
+    } else {
+        const int e = (int)(k & 7);
+        lane = (int)((k >> 3) & 63);
+        const int64_t rest = k >> 9;
+        const int ns = g.in_p / 16;
+        b = (int)(rest / ns);
+        step = (int)(rest % ns) * 8 + e;
     }
+    const int row = 32 * b + (lane & 31);
+    const int col = nf(lane >> 5, step);
+    if (row >= g.out_r || col >= g.in_r) return 0.0f;
+    return g.transpose ? params[g.src + (int64_t)col * g.ld + row]
+                       : params[g.src + (int64_t)row * g.ld + col];
 }
 
 static PackDesc pack_desc(const Net &net)
@@ -185,20 +179,9 @@ static PackDesc pack_desc(const Net &net)
     return d;
 }
 
-static void pack_images(const PackDesc &d, const float *src, float *img, void *img16,
-                        hipStream_t s)
-{
-    const int blocks = (int)std::min<int64_t>((d.total + 255) / 256, 1024);
-    hipLaunchKernelGGL(k_pack<false>, dim3(blocks), dim3(256), 0, s, d, src, img,
-                       (__bf16 *)nullptr);
-    if (img16)
-        hipLaunchKernelGGL(k_pack<true>, dim3(blocks), dim3(256), 0, s, d, src, (float *)nullptr,
-                           (__bf16 *)img16);
-}
-
-// The row-major image of the training kernel (MlpDesc::rm_off): layer L as
-// its padded rows x cols matrix, rows cols + 1 floats apart, zero outside
-// the real weights.
+// The row-major image of the gathering training kernel (MlpDesc::rm_off):
+// layer L as its padded rows x cols matrix, rows cols + 1 floats apart, zero
+// outside the real weights.
 struct RmDesc {
     int64_t off[NPM_MAX_LAYERS + 1];
     int64_t src[NPM_MAX_LAYERS];
@@ -206,42 +189,99 @@ struct RmDesc {
     int32_t n_layers;
 };
 
-__global__ void k_pack_rm(RmDesc d, const float *__restrict__ params, float *__restrict__ dst)
+__device__ __forceinline__ float rm_value(const RmDesc &d, int64_t i, const float *__restrict__ params)
 {
-    const int64_t total = d.off[d.n_layers];
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        int L = 0;
-        while (L + 1 < d.n_layers && i >= d.off[L + 1]) ++L;
-        const int64_t k = i - d.off[L];
-        const int S = d.cols[L] + 1;
-        const int o = (int)(k / S), c = (int)(k % S);
-        dst[i] = (o < d.out_r[L] && c < d.in_r[L]) ? params[d.src[L] + (int64_t)o * d.in_r[L] + c]
-                                                   : 0.0f;
+    int L = 0;
+    while (L + 1 < d.n_layers && i >= d.off[L + 1]) ++L;
+    const int64_t k = i - d.off[L];
+    const int S = d.cols[L] + 1;
+    const int o = (int)(k / S), c = (int)(k % S);
+    return (o < d.out_r[L] && c < d.in_r[L]) ? params[d.src[L] + (int64_t)o * d.in_r[L] + c] : 0.0f;
+}
+
+// Every image of a network's weights, and of their average (ema non-null), in
+// one launch: an element each of the FP32 image, the BF16 image (its backward
+// part with the two further planes of the three-way split, x = x0 + x1 + x2,
+// where `split` is set) and the row-major image, one after the other in the
+// index.  The grid's last block sums `nparts` FP64 partials into *sum (where
+// set).  One launch for what took up to six of 4 us each (a 16,384-vertex
+// training step of the 4-level network 101 -> 83 us, with the loss sum folded
+// into the weight-gradient sum).
+struct PackJob {
+    PackDesc d;
+    RmDesc r;
+    int64_t fwd, n_rm;             // elements of the forward image, of the row-major image (or 0)
+    const float *params, *ema;
+    float *img, *rm, *ema_img;
+    __bf16 *img16, *split, *ema_img16;
+    const double *part;
+    int nparts;
+    double *sum;
+};
+
+__global__ __launch_bounds__(256) void k_pack(PackJob j)
+{
+    if (j.sum && blockIdx.x == gridDim.x - 1) {
+        const double s = sum_partials(j.part, j.nparts);
+        if (threadIdx.x == 0) *j.sum = s;
+        return;
+    }
+    const int64_t T = j.d.total;
+    const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
+    if (i < T) {
+        j.img[i] = pack_value<false>(j.d, i, j.params);
+        if (j.ema) j.ema_img[i] = pack_value<false>(j.d, i, j.ema);
+    } else if (i < 2 * T) {
+        const int64_t k = i - T;
+        const float v = pack_value<true>(j.d, k, j.params);
+        const __bf16 v0 = (__bf16)v;
+        j.img16[k] = v0;
+        if (j.split && k >= j.fwd) {
+            const float r1 = v - (float)v0;
+            const __bf16 v1 = (__bf16)r1;
+            j.split[k - j.fwd] = v1;
+            j.split[T - j.fwd + k - j.fwd] = (__bf16)(r1 - (float)v1);
+        }
+        if (j.ema) j.ema_img16[k] = (__bf16)pack_value<true>(j.d, k, j.ema);
+    } else if (i < 2 * T + j.n_rm) {
+        j.rm[i - 2 * T] = rm_value(j.r, i - 2 * T, j.params);
     }
 }
 
-hipError_t launch_pack_mlp(npm_ctx *ctx, hipStream_t s)
+// nparts > 0: also sums ctx->partials into *sum.
+static hipError_t pack_images(npm_ctx *ctx, int nparts, double *sum, hipStream_t s)
 {
-    const PackDesc d = pack_desc(ctx->net);
-    pack_images(d, ctx->params, ctx->mlp_img, ctx->mlp_img16, s);
-    {
-        const Net &net = ctx->net;
-        RmDesc r{};
-        r.n_layers = net.lay.n_layers;
-        for (int i = 0; i < r.n_layers; ++i) {
-            r.off[i] = net.mlp.rm_off[i];
-            r.src[i] = net.lay.layer_offset[i];
-            r.cols[i] = i == 0 ? std::max(net.mlp.in_p, 32) : net.mlp.hid_p;
-            r.out_r[i] = net.lay.layer_out[i];
-            r.in_r[i] = net.lay.layer_in[i];
+    const Net &net = ctx->net;
+    const MlpDesc &m = net.mlp;
+    PackJob j{};
+    j.d = pack_desc(net);
+    j.fwd = m.fwd_elems;
+    j.params = ctx->params;
+    j.ema = ctx->ema;
+    j.img = ctx->mlp_img;
+    j.ema_img = ctx->ema_img;
+    j.img16 = (__bf16 *)ctx->mlp_img16;
+    j.split = (__bf16 *)ctx->mlp_split;
+    j.ema_img16 = (__bf16 *)ctx->ema_img16;
+    if (net.cfg.precision == NPM_PREC_FP32) {      // read by the FP32 training kernel only
+        j.n_rm = m.rm_elems;
+        j.rm = ctx->mlp_img + m.fwd_elems + m.bwd_elems;
+        j.r.n_layers = net.lay.n_layers;
+        for (int i = 0; i < j.r.n_layers; ++i) {
+            j.r.off[i] = m.rm_off[i];
+            j.r.src[i] = net.lay.layer_offset[i];
+            j.r.cols[i] = i == 0 ? std::max(m.in_p, 32) : m.hid_p;
+            j.r.out_r[i] = net.lay.layer_out[i];
+            j.r.in_r[i] = net.lay.layer_in[i];
         }
-        r.off[r.n_layers] = net.mlp.rm_elems;
-        const int blocks = (int)std::min<int64_t>((net.mlp.rm_elems + 255) / 256, 256);
-        hipLaunchKernelGGL(k_pack_rm, dim3(blocks), dim3(256), 0, s, r, ctx->params,
-                           ctx->mlp_img + net.mlp.fwd_elems + net.mlp.bwd_elems);
+        j.r.off[j.r.n_layers] = m.rm_elems;
     }
-    if (ctx->ema) pack_images(d, ctx->ema, ctx->ema_img, ctx->ema_img16, s);
+    j.part = ctx->partials;
+    j.nparts = nparts;
+    j.sum = nparts > 0 ? sum : nullptr;
+    const int64_t elems = 2 * j.d.total + j.n_rm;
+    const int blocks = (int)((elems + 255) / 256) + (j.sum ? 1 : 0);
+    hipLaunchKernelGGL(k_pack, dim3(blocks), dim3(256), 0, s, j);
     return hipGetLastError();
 }
 
@@ -254,7 +294,7 @@ __global__ void k_grid_to_half(const float *__restrict__ p, __half *__restrict__
 
 hipError_t launch_refresh_lowp(npm_ctx *ctx, hipStream_t s)
 {
-    hipError_t e = launch_pack_mlp(ctx, s);
+    const hipError_t e = pack_images(ctx, 0, nullptr, s);
     if (e != hipSuccess) return e;
     const int64_t n = ctx->net.lay.grid_params;
     if (ctx->grid16)
@@ -324,36 +364,19 @@ hipError_t launch_adam(npm_ctx *ctx, float *grad, double *gradnorm_out, hipStrea
                        (__half *)ctx->grid16, ctx->net.lay.grid_params, ctx->partials, ctx->ema,
                        (__half *)ctx->ema_grid16, c.ema_decay);
     timed_end(ctx, tok, s);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // the packed MLP images (and their BF16 copy) follow the new weights
-    e = launch_pack_mlp(ctx, s);
-    if (e != hipSuccess) return e;
-    if (gradnorm_out) return launch_reduce_partials(ctx, blocks, gradnorm_out, s);
-    return hipSuccess;
+    // the packed MLP images follow the new weights; with them the gradient norm
+    return pack_images(ctx, gradnorm_out ? blocks : 0, gradnorm_out, s);
 }
 
 // ---------------------------------------------------------------- reductions
 // Sums nparts FP64 partials in a fixed order into *out (times scale).
-__global__ void k_reduce(const double *__restrict__ part, int nparts, double scale,
-                         double *__restrict__ out)
+__global__ __launch_bounds__(256) void k_reduce(const double *__restrict__ part, int nparts,
+                                                double scale, double *__restrict__ out)
 {
-    __shared__ double red[256];
-    double a = 0.0;
-    for (int i = threadIdx.x; i < nparts; i += 256) a += part[i];
-    red[threadIdx.x] = a;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = red[0] * scale;
-}
-
-hipError_t launch_reduce_partials(npm_ctx *ctx, int nparts, double *out, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(256), 0, s, ctx->partials, nparts, 1.0, out);
-    return hipGetLastError();
+    const double s = sum_partials(part, nparts);
+    if (threadIdx.x == 0) *out = s * scale;
 }
 
 hipError_t launch_reduce_scaled(const double *part, int nparts, double scale, double *out,

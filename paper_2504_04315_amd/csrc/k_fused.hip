@@ -205,7 +205,7 @@ __global__ __launch_bounds__(64 * WV) void k_backward_fused(FusedArgs a, int mlp
                                                                   acts[NH - 1], o, lane);
         }
         float d[16];
-        const float lv = kl_head(o, in, valid, io.invN, h, d, lacc);
+        const float lv = kl_head<!BF>(o, in, valid, io.invN, h, d, lacc);
         float ds = 0.0f;            // SEL: d loss / d c'
         if constexpr (SEL) {
             const float cp = select_logit<HID_P>(s_wsel, acts[NH - 1], h);
@@ -376,10 +376,23 @@ __global__ __launch_bounds__(256) void k_scatter_tiles(GridDesc g, int64_t n,
 // Sum of the blocks' weight-gradient partials into the gradient: a block of
 // 256 threads covers 16 weights, its 16 thread rows a sixteenth of the
 // partials each (several loads in flight per thread, 768 blocks at the
-// production size), then the rows add in LDS.
+// production size), then the rows add in LDS.  The blocks past the weights'
+// sum the FP64 loss partials: one the mixture's (loss set), one the selection
+// term's (loss_sel set).
 __global__ __launch_bounds__(256) void k_dw_sum(const float *__restrict__ part, int nparts,
-                                                int count, float *__restrict__ grad)
+                                                int count, float *__restrict__ grad,
+                                                const double *__restrict__ lpart, double lscale,
+                                                double *__restrict__ loss,
+                                                const double *__restrict__ lpart_sel,
+                                                double *__restrict__ loss_sel)
 {
+    const int wblocks = (count + 15) / 16;
+    if ((int)blockIdx.x >= wblocks) {
+        const bool sel = (int)blockIdx.x > wblocks;
+        const double s = sum_partials(sel ? lpart_sel : lpart, nparts);
+        if (threadIdx.x == 0) *(sel ? loss_sel : loss) = s * lscale;
+        return;
+    }
     __shared__ float red[16][17];
     const int x = threadIdx.x & 15, y = threadIdx.x >> 4;
     const int i = blockIdx.x * 16 + x;
@@ -403,26 +416,11 @@ __global__ __launch_bounds__(256) void k_dw_sum(const float *__restrict__ part, 
 }
 
 // ------------------------------------------------------------------ launch
-// Blocks of the training kernel: one per compute unit at most (the weight
-// image and the exchange buffer take most of its LDS), WV waves each.
-constexpr int kTrainWaves = 4;
-constexpr int kTrainMaxBlocks = 256;
-static int backward_blocks(int64_t n)
-{
-    const int64_t tiles = (n + 31) / 32;
-    return (int)std::max<int64_t>(1, std::min<int64_t>((tiles + kTrainWaves - 1) / kTrainWaves,
-                                                       kTrainMaxBlocks));
-}
-
-// Dynamic LDS a training block may take: gfx950's 160 KB per workgroup less
-// room for the kernel's static arrays (level table, FP64 loss partials).
-constexpr size_t kLdsBytes = 160 * 1024 - 4096;
-
 template <int IN_P, int HID_P, int NH, int F, bool BF, int PG = 0, bool SEL = false>
 static hipError_t run_backward(npm_ctx *ctx, FusedArgs a, hipStream_t s)
 {
     using Plan = BlockPlan<IN_P, HID_P, NH, kTrainWaves>;
-    const int blocks = backward_blocks(a.n);
+    const int blocks = train_blocks(a.n);
     const size_t img = BF ? (size_t)staged_elems(a, IN_P, HID_P, PG) * 2
                           : (size_t)Plan::rm_elems() * 4;
     if (!BF && (int64_t)Plan::rm_elems() != ctx->net.mlp.rm_elems) return hipErrorInvalidValue;
@@ -466,7 +464,8 @@ bool fused_shape_supported(const Net &net)
 hipError_t fused_backward(npm_ctx *ctx, int64_t n, const float *pos, const float *aux,
                           const float *dir, const float *rad, const float *spdf, float *grad,
                           double *loss_out, const uint32_t *perm, const float *rec,
-                          float *dg_tiles, const BinDesc *bins, hipStream_t s, const float *bsdf)
+                          float *dg_tiles, const BinDesc *bins, hipStream_t s, const float *bsdf,
+                          void *feat)
 {
     FusedArgs a = fused_args(ctx, n, pos);
     a.aux = aux;
@@ -483,13 +482,25 @@ hipError_t fused_backward(npm_ctx *ctx, int64_t n, const float *pos, const float
     a.wsel = selection_row(ctx, ctx->params);
     a.bsdf = bsdf;
     a.partials_sel = ctx->partials + kPartials / 2;
+    const bool b16 = ctx->net.cfg.precision == NPM_PREC_BF16;
+    a.img_t = (const __bf16 *)ctx->mlp_img16 + ctx->net.mlp.fwd_elems;
+    a.img_split = (const __bf16 *)ctx->mlp_split;
     hipError_t e = hipSuccess;
     int tok;
+    if (feat && grad) {
+        a.feat = feat;
+        timed_begin(ctx, "train_encode", s, &tok);
+        e = launch_grid_encode(ctx->net.grid, n, pos, a.rec, a.rec_stride, a.grid32, a.grid16, b16,
+                               feat, s);
+        timed_end(ctx, tok, s);
+        if (e != hipSuccess) return e;
+    }
     timed_begin(ctx, "fused_backward", s, &tok);
-    NPM_FUSED_RUN(run_backward);
+    if (a.feat) e = train_tile(ctx, a, s);
+    else NPM_FUSED_RUN(run_backward);
     timed_end(ctx, tok, s);
     if (e != hipSuccess) return e;
-    const int blocks = backward_blocks(n);
+    const int blocks = train_blocks(n);
     if (grad) {
         const int64_t tiles = (n + 31) / 32;
         const int64_t waves = std::min<int64_t>(tiles, 4096);
@@ -529,8 +540,12 @@ hipError_t fused_backward(npm_ctx *ctx, int64_t n, const float *pos, const float
         }
         const int count = (int)(ctx->net.lay.n_params - ctx->net.lay.grid_params);
         timed_begin(ctx, "fused_dw_sum", s2, &tok);
-        hipLaunchKernelGGL(k_dw_sum, dim3((count + 15) / 16), dim3(256), 0, s2, ctx->s_dw_part,
-                           blocks, count, grad + ctx->net.lay.grid_params);
+        // with the weights' sum the losses', a block each
+        double *lsel = loss_out && bsdf && a.wsel ? loss_out + 1 : nullptr;
+        hipLaunchKernelGGL(k_dw_sum, dim3((count + 15) / 16 + (loss_out ? 1 : 0) + (lsel ? 1 : 0)),
+                           dim3(256), 0, s2, ctx->s_dw_part, blocks, count,
+                           grad + ctx->net.lay.grid_params, ctx->partials, 1.0 / (double)n, loss_out,
+                           a.partials_sel, lsel);
         timed_end(ctx, tok, s2);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -542,7 +557,7 @@ hipError_t fused_backward(npm_ctx *ctx, int64_t n, const float *pos, const float
             if (e != hipSuccess) return e;
         }
     }
-    if (!loss_out) return hipSuccess;
+    if (!loss_out || grad) return hipSuccess;
     e = launch_reduce_scaled(ctx->partials, blocks, 1.0 / (double)n, loss_out, s);
     if (e != hipSuccess || !(bsdf && a.wsel)) return e;
     return launch_reduce_scaled(a.partials_sel, blocks, 1.0 / (double)n, loss_out + 1, s);

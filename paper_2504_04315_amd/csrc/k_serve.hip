@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256) void k_serve_train(RoundHdr *hdr, const DevReq
             tile_input<IN_P, F, true, 0>(gv, io, in, vs, vs, h, x);
             float acts[NH][HID_P / 2], o[16], d[16];
             mlp_forward<IN_P, HID_P, NH, true, true>(fwd, x, acts, o, lane);
-            kl_head(o, in, valid, io.invN, h, d, lacc);
+            kl_head<false>(o, in, valid, io.invN, h, d, lacc);
             // ---- output layer's dW, then the delta chain
             float dh[HID_P / 2];
             dw_phase<Plan, NH, WV, XS>(xb, d, acts[NH - 1], wave, acc, lane);

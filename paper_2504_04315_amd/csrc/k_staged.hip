@@ -426,7 +426,7 @@ __global__ __launch_bounds__(256) void k_loss_grad(int64_t n, const float *__res
             const float g = -wgt * invN;
 #pragma unroll
             for (int k = 0; k < kLobes; ++k)
-                lobe_grad(L[k], r[4 * k], r[4 * k + 1], r[4 * k + 2], expf(lt[k] - lv),
+                lobe_grad<true>(L[k], r[4 * k], r[4 * k + 1], r[4 * k + 2], expf(lt[k] - lv),
                           expf(L[k].loglam), g, wx, wy, wz, out + 4 * k);
             lacc -= (double)wgt * (double)lv;
             if (sel && bsdf) {

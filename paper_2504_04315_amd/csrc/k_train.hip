@@ -1,0 +1,544 @@
+// The training tile kernel: MLP forward, KL-gradient head (Sec. 4.2, eq.
+// mcgradients), delta chain and weight gradients of a batch whose grid features
+// were encoded level by level before (k_encode.hip); the tile's dG is stored
+// for the scatter passes.
+//
+// What bounds it.  FP32 matrix instructions run on the vector unit's
+// multipliers on this chip: a wave's FP32 products and any wave's vector
+// instructions add up (matrix 250 us and vector 273 us of work take 511 us
+// together), while BF16 products run beside vector work at 16 times the rate.
+// So the FP32 form keeps FP32 instructions only where their exact sums decide
+// something -- the forward pass, whose sign selects each ReLU -- and forms the
+// products of the backward pass from operands split into three BF16 numbers
+// (below): 24,576 of the 36,864 FP32 matrix cycles of a tile become 9,216 BF16
+// ones that overlap the rest.
+//
+// Split operands: x = x0 + x1 + x2 exactly (8 + 8 + 8 significand bits, each
+// remainder of a round-to-nearest BF16 conversion is exact in FP32), and the
+// six products x0 y0, x0 y1, x1 y0, x1 y1, x0 y2, x2 y0 (Henry, Tang and
+// Heinecke, 2019) leave out terms below 2^-26 of the product, accumulated in
+// FP32 over 16 terms an instruction instead of 2.
+//
+// A wave is on its own from tile to tile: it keeps all weight-gradient blocks
+// in accumulators (192 registers of the 512 a wave has at one per SIMD) and
+// transposes its deltas and layer inputs itself, one 32-row block at a time,
+// because the tile's vertices are the reduction dimension there.  No barrier
+// stands between a block's waves; their weight gradients meet in LDS once at
+// the end.
+//
+// Measured against the kernel that gathers (k_fused.hip), this one with its
+// encode: 2^20 vertices on the 16-level hash grid FP32 1,075 -> 248 + 636 us,
+// BF16 585 -> 198 + 240; NPM-product BF16, 300,001 vertices, 247 -> 79 + 113;
+// 8-level dense grid FP32, 2^18 vertices, 179 -> 20 + 137.  What bounds it now:
+// FP32 form, FP32 matrix 12.3k and vector 17k of 45k cycles a tile, the rest
+// BF16 products that a single wave does not overlap; precision form, vector
+// instructions (13k of 17k cycles).
+#include <type_traits>
+
+#include "fused_launch.h"
+
+namespace npm {
+
+namespace {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+template <bool BF> constexpr int kPlanes = BF ? 1 : 3;
+
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
+{
+    const bf16x2 v = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(uint32_t, v);
+}
+__device__ __forceinline__ float lo_f32(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float hi_f32(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// R registers of a tile-layout vector as BF16 planes, two registers a word:
+// one plane in the precision form, the three-way split in FP32.
+template <int R, bool BF> struct Planes {
+    uint32_t w[kPlanes<BF>][R / 2];
+
+    __device__ __forceinline__ void set(const float *x)
+    {
+#pragma unroll
+        for (int i = 0; i < R / 2; ++i) {
+            float a = x[2 * i], b = x[2 * i + 1];
+#pragma unroll
+            for (int p = 0; p < kPlanes<BF>; ++p) {
+                w[p][i] = pack_bf16(a, b);
+                if (p + 1 < kPlanes<BF>) {
+                    a -= lo_f32(w[p][i]);
+                    b -= hi_f32(w[p][i]);
+                }
+            }
+        }
+    }
+    // matrix operand of registers [8 s, 8 s + 8), plane p
+    __device__ __forceinline__ bf16x8 op(int p, int s) const
+    {
+        const uint4 v = {w[p][4 * s], w[p][4 * s + 1], w[p][4 * s + 2], w[p][4 * s + 3]};
+        return __builtin_bit_cast(bf16x8, v);
+    }
+};
+
+// The planes' products from the smallest up: A[pa(i)] B[pb(i)], i = 0 .. N - 1.
+template <bool BF> struct Products {
+    static constexpr int N = BF ? 1 : 6;
+    static constexpr int pa(int i) { return BF ? 0 : (int[]){2, 0, 1, 1, 0, 0}[i]; }
+    static constexpr int pb(int i) { return BF ? 0 : (int[]){0, 2, 1, 0, 1, 0}[i]; }
+};
+
+__device__ __forceinline__ f32x16 zero16()
+{
+    f32x16 z;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) z[v] = 0.0f;
+    return z;
+}
+
+// y (M wide) = W^T d for the planes d of a K-wide vector; img: plane p of the
+// packed BF16 image of W^T at img + p * stride (device_math.h's layout).
+template <int K, int M, bool BF>
+__device__ __forceinline__ void chain_layer(const __bf16 *img, int stride, const Planes<K / 2, BF> &d,
+                                            float *y, int lane)
+{
+    constexpr int NB = M / 32, NS = K / 16, P = kPlanes<BF>;
+    f32x16 acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = zero16();
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        bf16x8 A[NB][P];
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                A[b][p] = *reinterpret_cast<const bf16x8 *>(img + p * stride + ((b * NS + s) * 64 + lane) * 8);
+        // the blocks in turn: two products in a row never wait for one sum
+#pragma unroll
+        for (int i = 0; i < Products<BF>::N; ++i)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[b][Products<BF>::pa(i)],
+                                                                 d.op(Products<BF>::pb(i), s), acc[b], 0, 0, 0);
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) y[16 * b + v] = acc[b][v];
+}
+
+// A 32-row block with the tile's 32 vertices as the reduction dimension: lane
+// i % 32 holds row i, and of the step s the half-wave h the vertices
+// nf(h, 8 s + e).  The matrix unit transposes: with the block's planes as the
+// left operand (rows = vertices) and the identity as the right one, the product
+// has the block's rows as its columns, exactly (one term each), and its
+// registers are the next operands.  Through LDS the same transposition took 16
+// two-byte writes a block and plane and waited for its reads (8-level network,
+// 2^18 vertices FP32, 160 -> 142 us; NPM-product in BF16, 300,001 vertices, 168
+// -> 135 us).
+struct Identity {
+    bf16x8 k[2];
+    __device__ __forceinline__ explicit Identity(int lane)
+    {
+        const int n = lane & 31, h = lane >> 5;
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) k[s][e] = (__bf16)(n == nf(h, 8 * s + e) ? 1.0f : 0.0f);
+    }
+};
+template <bool BF> struct Rows {
+    bf16x8 k[2][kPlanes<BF>];
+
+    // the registers [16 blk, 16 blk + 16) of v
+    template <int R>
+    __device__ __forceinline__ void load(const Identity &id, const Planes<R, BF> &v, int blk)
+    {
+        f32x16 t[kPlanes<BF>];
+#pragma unroll
+        for (int p = 0; p < kPlanes<BF>; ++p)
+            t[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v.op(p, 2 * blk), id.k[0], zero16(), 0, 0, 0);
+#pragma unroll
+        for (int p = 0; p < kPlanes<BF>; ++p)
+            t[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v.op(p, 2 * blk + 1), id.k[1], t[p], 0, 0, 0);
+#pragma unroll
+        for (int p = 0; p < kPlanes<BF>; ++p)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                uint32_t w[4];
+                // the values are BF16 numbers: the upper halves of their FP32 forms
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    w[i] = __builtin_amdgcn_perm(__float_as_uint(t[p][8 * s + 2 * i + 1]),
+                                                 __float_as_uint(t[p][8 * s + 2 * i]), 0x07060302u);
+                k[s][p] = __builtin_bit_cast(bf16x8, uint4{w[0], w[1], w[2], w[3]});
+            }
+    }
+};
+
+// Weight-gradient blocks (32 x 32) of a network, layer by layer from the
+// output layer down, each layer's blocks row block by row block.
+template <int IN_P, int HID_P, int NH> struct DwBlocks {
+    static constexpr int IN0 = IN_P < 32 ? 32 : IN_P;
+    static constexpr int out_p(int L) { return L == NH ? 32 : HID_P; }
+    static constexpr int in_p(int L) { return L == 0 ? IN0 : HID_P; }
+    static constexpr int nbi(int L) { return in_p(L) / 32; }
+    static constexpr int blocks(int L) { return (out_p(L) / 32) * nbi(L); }
+    static constexpr int first(int L)
+    {
+        int g = 0;
+        for (int l = NH; l > L; --l) g += blocks(l);
+        return g;
+    }
+    static constexpr int total() { return first(-1); }
+};
+
+}  // namespace
+
+// SEL: the network has the selection output (k_fused.hip); the row's gradient is
+// kept per lane (its vertices' share of each feature) and summed at the end.
+template <int IN_P, int HID_P, int NH, int F, bool BF, int PG, bool SEL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_train_tile(FusedArgs a, int mlp_weights,
+                                                                                              int fwd_bytes, int t_elems)
+{
+    using DB = DwBlocks<IN_P, HID_P, NH>;
+    constexpr int IN0 = DB::IN0, P = kPlanes<BF>, NDW = DB::total();
+    constexpr int DGR = PG > 0 ? 32 : IN0;      // input-gradient rows (grid features only with PG)
+    constexpr int ING = PG > 0 ? ProductShape<PG>::GF : IN_P;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    __shared__ double red[256];
+    __shared__ __attribute__((aligned(16))) float s_wsel[SEL ? HID_P : 4];
+    // LDS: the forward image, the planes of the backward (W^T) image
+    const char *fwd = smem;
+    __bf16 *bwd = reinterpret_cast<__bf16 *>(smem + fwd_bytes);
+    for (int i = threadIdx.x; i < fwd_bytes / 16; i += 256)
+        reinterpret_cast<f32x4 *>(smem)[i] = reinterpret_cast<const f32x4 *>(a.img)[i];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const f32x4 *src = reinterpret_cast<const f32x4 *>(p == 0 ? a.img_t : a.img_split + (size_t)(p - 1) * a.bwd_elems);
+        for (int i = threadIdx.x; i < t_elems / 8; i += 256)
+            reinterpret_cast<f32x4 *>(bwd + p * t_elems)[i] = src[i];
+    }
+    if constexpr (SEL)
+        for (int i = threadIdx.x; i < HID_P; i += 256) s_wsel[i] = i < a.width ? a.wsel[i] : 0.0f;
+    __syncthreads();
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, h = lane >> 5;
+    // FP32, three hidden layers: the first one's activations wait in LDS (8 KB a
+    // wave), and the input features are read again for their weight gradient
+    constexpr bool PARK = !BF && NH >= 3;
+    f32x4 *park = reinterpret_cast<f32x4 *>(bwd + P * t_elems) + wave * (HID_P / 8 * 64) + lane;
+    const Identity id(lane);
+    const TrainIO io{a.n, a.pos, a.dir, a.rad, a.spdf, a.grad, a.invN, a.perm, a.rec, a.aux,
+                     a.rec_stride, a.bsdf};
+    const int gf = a.g.n_levels * F;
+    f32x16 acc[NDW];
+#pragma unroll
+    for (int k = 0; k < NDW; ++k) acc[k] = zero16();
+    float selacc[SEL ? HID_P / 2 : 1];
+#pragma unroll
+    for (int i = 0; i < (SEL ? HID_P / 2 : 1); ++i) selacc[i] = 0.0f;
+    double lacc = 0.0, lsel = 0.0;
+    const int64_t n = a.n, ntiles = (n + 31) / 32;
+    const int64_t nwaves = (int64_t)gridDim.x * 4;
+    auto slot = [&](int64_t t) {
+        const int64_t v = t * 32 + (lane & 31);
+        return v < n ? v : n - 1;
+    };
+    int64_t t = blockIdx.x * (int64_t)4 + wave;
+    FeatWords<ING, BF> fw;
+    TrainInputs in_next;
+    if (t < ntiles) {
+        feat_load<ING, BF>(a.feat, gf, n, slot(t), h, fw);
+        in_next = train_inputs(io, slot(t), slot(t));
+    }
+    for (; t < ntiles; t += nwaves) {
+        const bool valid = t * 32 + (lane & 31) < n;
+        const TrainInputs in = in_next;
+        float x[IN0 / 2];
+        feat_take<IN_P, ING, BF>(fw, gf, h, x);
+#pragma unroll
+        for (int i = IN_P / 2; i < IN0 / 2; ++i) x[i] = 0.0f;
+        if constexpr (PG > 0) {
+            float a7[7];
+            load_aux(io.rec, io.rec_stride, io.aux, n, slot(t), slot(t), a7);
+            aux_fill<IN_P, ProductShape<PG>::GF, ProductShape<PG>::SHD>(h, a7, x);
+        }
+        // the next tile's inputs, in flight during this one
+        if (t + nwaves < ntiles) {
+            feat_load<ING, BF>(a.feat, gf, n, slot(t + nwaves), h, fw);
+            in_next = train_inputs(io, slot(t + nwaves), slot(t + nwaves));
+        }
+        // ---- forward
+        float o[16], cp = 0.0f;
+        float acts[BF ? 1 : NH][HID_P / 2];           // FP32 form
+        Planes<HID_P / 2, true> ap[BF ? NH : 1];      // precision form: the activations as used
+        Planes<IN0 / 2, BF> xp;
+        if constexpr (BF) {
+            xp.set(x);
+            float y[HID_P / 2];
+            mfma_layer_bf16<IN_P, HID_P>(reinterpret_cast<const __bf16 *>(fwd), x, y, lane);
+#pragma unroll
+            for (int li = 0; li < NH; ++li) {
+#pragma unroll
+                for (int i = 0; i < HID_P / 2; ++i) y[i] = fmaxf(y[i], 0.0f);
+                if constexpr (SEL)
+                    if (li == NH - 1) cp = select_logit<HID_P>(s_wsel, y, h);
+                ap[li].set(y);
+                const __bf16 *im = reinterpret_cast<const __bf16 *>(fwd) + HID_P * IN_P + li * HID_P * HID_P;
+                if (li + 1 < NH) {
+                    float z[HID_P / 2];
+                    mfma_layer_bf16<HID_P, HID_P>(im, y, z, lane);
+#pragma unroll
+                    for (int i = 0; i < HID_P / 2; ++i) y[i] = z[i];
+                } else {
+                    mfma_layer_bf16<HID_P, 32>(im, y, o, lane);
+                }
+            }
+        } else {
+            const float *im = reinterpret_cast<const float *>(fwd);
+            mfma_layer_f32<IN_P, HID_P>(im, x, acts[0], lane);
+            im += HID_P * IN_P;
+#pragma unroll
+            for (int li = 0; li < NH; ++li) {
+#pragma unroll
+                for (int i = 0; i < HID_P / 2; ++i) acts[li][i] = fmaxf(acts[li][i], 0.0f);
+                if (li + 1 < NH) mfma_layer_f32<HID_P, HID_P>(im, acts[li], acts[li + 1 < NH ? li + 1 : 0], lane);
+                else mfma_layer_f32<HID_P, 32>(im, acts[li], o, lane);
+                im += HID_P * HID_P;
+                if (PARK && li == 0) {
+#pragma unroll
+                    for (int q = 0; q < HID_P / 8; ++q)
+                        park[q * 64] = f32x4{acts[0][4 * q], acts[0][4 * q + 1], acts[0][4 * q + 2], acts[0][4 * q + 3]};
+                }
+            }
+            if constexpr (SEL) cp = select_logit<HID_P>(s_wsel, acts[NH - 1], h);
+        }
+        // ---- head
+        float d[16];
+        const float lv = kl_head<!BF>(o, in, valid, io.invN, h, d, lacc);
+        float ds = 0.0f;            // SEL: d loss / d c'
+        if constexpr (SEL) {
+            const float wgt = valid ? sample_weight(in.rad, in.spdf) : 0.0f;
+            if (wgt != 0.0f && io.bsdf) {
+                const float pb = io.bsdf[visit(io.perm, slot(t))];
+                if (bsdf_valid(pb)) {
+                    const float lpc = select_term(cp, pb, lv, -wgt * io.invN, ds);
+                    if (h == 0) lsel -= (double)wgt * (double)lpc;
+                }
+            }
+        }
+        // hidden unit i of layer li is on / the value its weight gradient takes
+        auto on = [&](int li, int i) {
+            if constexpr (BF) {
+                const uint32_t w = ap[li].w[0][i >> 1];
+                return ((i & 1) ? (w >> 16) : (w & 0xffffu)) != 0u;
+            } else {
+                return acts[li][i] > 0.0f;
+            }
+        };
+        if constexpr (SEL) {
+#pragma unroll
+            for (int i = 0; i < HID_P / 2; ++i) {
+                float v;
+                if constexpr (BF) {
+                    const uint32_t w = ap[NH - 1].w[0][i >> 1];
+                    v = (i & 1) ? hi_f32(w) : lo_f32(w);
+                } else {
+                    v = acts[NH - 1][i];
+                }
+                selacc[i] = fmaf(ds, v, selacc[i]);
+            }
+        }
+        // ---- per layer from the output layer down: the delta's planes, the
+        // next delta, this layer's weight gradient
+        float dh[HID_P / 2];
+        const __bf16 *im = bwd;
+        auto weight_gradient = [&](auto LC, const auto &dp, const auto &inp) {
+            constexpr int L = decltype(LC)::value;
+            constexpr int NBO = DB::out_p(L) / 32, NBI = DB::nbi(L);
+            Rows<BF> rd[NBO];
+#pragma unroll
+            for (int b = 0; b < NBO; ++b) rd[b].load(id, dp, b);
+#pragma unroll
+            for (int c = 0; c < NBI; ++c) {
+                Rows<BF> ri;
+                ri.load(id, inp, c);
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int i = 0; i < Products<BF>::N; ++i)
+#pragma unroll
+                        for (int b = 0; b < NBO; ++b) {
+                            f32x16 &q = acc[DB::first(L) + b * NBI + c];
+                            q = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rd[b].k[s][Products<BF>::pa(i)],
+                                                                        ri.k[s][Products<BF>::pb(i)], q, 0, 0, 0);
+                        }
+            }
+        };
+        {
+            Planes<16, BF> dp;
+            dp.set(d);
+            chain_layer<32, HID_P, BF>(im, t_elems, dp, dh, lane);
+            im += HID_P * 32;
+            if constexpr (SEL) {
+#pragma unroll
+                for (int q = 0; q < HID_P / 8; ++q) {
+                    const f32x4 w = *reinterpret_cast<const f32x4 *>(s_wsel + 8 * q + 4 * h);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) dh[4 * q + e] = fmaf(ds, w[e], dh[4 * q + e]);
+                }
+            }
+            if constexpr (BF) {
+                weight_gradient(std::integral_constant<int, NH>{}, dp, ap[NH - 1]);
+            } else {
+                Planes<HID_P / 2, BF> ip;
+                ip.set(acts[NH - 1]);
+                weight_gradient(std::integral_constant<int, NH>{}, dp, ip);
+            }
+        }
+        static_for_down<NH - 1, 1>([&](auto LC) {
+            constexpr int li = decltype(LC)::value;
+#pragma unroll
+            for (int i = 0; i < HID_P / 2; ++i) dh[i] = on(li, i) ? dh[i] : 0.0f;
+            if constexpr (PARK && li == 1) {
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int q = 0; q < HID_P / 8; ++q) {
+                    const f32x4 v = park[q * 64];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acts[0][4 * q + e] = v[e];
+                }
+            }
+            Planes<HID_P / 2, BF> dp;
+            dp.set(dh);
+            chain_layer<HID_P, HID_P, BF>(im, t_elems, dp, dh, lane);
+            im += HID_P * HID_P;
+            if constexpr (BF) {
+                weight_gradient(LC, dp, ap[li - 1]);
+            } else {
+                Planes<HID_P / 2, BF> ip;
+                ip.set(acts[li - 1]);
+                weight_gradient(LC, dp, ip);
+            }
+        });
+        {
+#pragma unroll
+            for (int i = 0; i < HID_P / 2; ++i) dh[i] = on(0, i) ? dh[i] : 0.0f;
+            Planes<HID_P / 2, BF> dp;
+            dp.set(dh);
+            float dG[DGR / 2];
+            chain_layer<HID_P, DGR, BF>(im, t_elems, dp, dG, lane);
+            float *dst = a.dg_tiles + (size_t)t * IN0 * 32 + (lane & 31) + 4 * h * 32;
+#pragma unroll
+            for (int q = 0; q < DGR / 2; ++q) dst[nf(0, q) * 32] = dG[q];
+            if constexpr (!BF) {
+                if constexpr (PARK) {
+                    FeatWords<ING, BF> again;
+                    feat_load<ING, BF>(a.feat, gf, n, slot(t), h, again);
+                    feat_take<IN_P, ING, BF>(again, gf, h, x);
+                }
+                xp.set(x);
+            }
+            weight_gradient(std::integral_constant<int, 0>{}, dp, xp);
+        }
+    }
+    // ---- loss partials of the block (FP64)
+    auto block_sum = [&](double v) {
+        __syncthreads();
+        red[threadIdx.x] = v;
+        __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+            __syncthreads();
+        }
+        return red[0];
+    };
+    const double lsum = block_sum(lacc);
+    if (threadIdx.x == 0) a.partials[blockIdx.x] = lsum;
+    if constexpr (SEL) {
+        const double ssum = block_sum(lsel);
+        if (threadIdx.x == 0) a.partials_sel[blockIdx.x] = ssum;
+    }
+    // ---- the waves' weight gradients meet in LDS (the images are no longer
+    // read), one 32x32 block of 1,024 floats after the other, and go out in the
+    // flat layout of the MLP weights (entries outside the real shapes dropped)
+    float *sum = reinterpret_cast<float *>(smem);
+    for (int w = 0; w < 4; ++w) {
+        __syncthreads();
+        if (wave == w) {
+#pragma unroll
+            for (int g = 0; g < NDW; ++g)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    float *q = sum + g * 1024 + r * 64 + lane;
+                    *q = w == 0 ? acc[g][r] : *q + acc[g][r];
+                }
+        }
+    }
+    __syncthreads();
+    float *out = a.dw_part + (int64_t)blockIdx.x * mlp_weights;
+    static_for_down<NH, 0>([&](auto LC) {
+        constexpr int L = decltype(LC)::value;
+        const int out_r = L == NH ? 32 : a.width, in_r = L == 0 ? a.n_in : a.width;
+        float *o = out + (L == 0 ? 0 : a.width * a.n_in + (L - 1) * a.width * a.width);
+        for (int i = threadIdx.x; i < DB::blocks(L) * 1024; i += 256) {
+            const int b = i >> 10, r = (i >> 6) & 15, ln = i & 63;
+            const int row = 32 * (b / DB::nbi(L)) + nf(ln >> 5, r), col = 32 * (b % DB::nbi(L)) + (ln & 31);
+            if (row < out_r && col < in_r) o[row * in_r + col] = sum[DB::first(L) * 1024 + i];
+        }
+    });
+    if constexpr (SEL) {
+        // the selection row (after the output layer's 32 rows): every vertex's
+        // share of each feature, over the half-wave's lanes and the waves
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < HID_P / 2; ++i) {
+            float v = selacc[i];
+#pragma unroll
+            for (int m = 1; m < 32; m <<= 1) v += __shfl_xor(v, m, 64);
+            if ((lane & 31) == 0) sum[wave * HID_P + nf(h, i)] = v;
+        }
+        __syncthreads();
+        if ((int)threadIdx.x < a.width) {
+            float v = 0.0f;
+            for (int w = 0; w < 4; ++w) v += sum[w * HID_P + threadIdx.x];
+            const int64_t row = (int64_t)a.width * a.n_in + (int64_t)(NH - 1) * a.width * a.width + 32 * a.width;
+            out[row + threadIdx.x] = v;
+        }
+    }
+}
+
+// ------------------------------------------------------------------ launch
+template <int IN_P, int HID_P, int NH, int F, bool BF, int PG = 0, bool SEL = false>
+static hipError_t run_train(npm_ctx *ctx, FusedArgs a, hipStream_t s)
+{
+    using DB = DwBlocks<IN_P, HID_P, NH>;
+    if constexpr (IN_P > 32 && !BF) {
+        return hipErrorNotSupported;      // the images and their planes exceed the LDS
+    } else {
+        // of W_0^T, the last segment, only the input-gradient rows are needed
+        const int t_elems = a.bwd_elems - (DB::IN0 - (PG > 0 ? 32 : DB::IN0)) * HID_P;
+        const int fwd_bytes = a.fwd_elems * (BF ? 2 : 4);
+        const size_t lds = std::max<size_t>((size_t)fwd_bytes + (size_t)kPlanes<BF> * t_elems * 2 +
+                                                (!BF && NH >= 3 ? 4 * HID_P / 2 * 64 * 4 : 0),
+                                            (size_t)DB::total() * 4096);
+        if (lds > kLdsBytes) return hipErrorInvalidValue;
+        auto k = k_train_tile<IN_P, HID_P, NH, F, BF, PG, SEL>;
+        const hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        const int count = (int)(ctx->net.lay.n_params - ctx->net.lay.grid_params);
+        hipLaunchKernelGGL(k, dim3(train_blocks(a.n)), dim3(256), lds, s, a, count, fwd_bytes, t_elems);
+        return hipGetLastError();
+    }
+}
+
+hipError_t train_tile(npm_ctx *ctx, const FusedArgs &args, hipStream_t s)
+{
+    FusedArgs a = args;
+    hipError_t e = hipSuccess;
+    NPM_FUSED_RUN(run_train);
+    return e;
+}
+
+}  // namespace npm

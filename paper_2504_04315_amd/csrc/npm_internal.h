@@ -81,6 +81,8 @@ struct npm_ctx {
     // Packed MLP weight images (forward and backward), FP32 and BF16
     float *mlp_img = nullptr;          // [fwd_elems + bwd_elems + rm_elems] FP32
     void *mlp_img16 = nullptr;         // [fwd_elems + bwd_elems] BF16
+    void *mlp_split = nullptr;         // [2][bwd_elems] BF16: the backward image's two further
+                                       // planes (FP32 form: weight = sum of three BF16 numbers)
     // Exponential moving average of the parameters (ema_decay > 0): FP32
     // master, its packed images and (NPM_PREC_BF16) its FP16 grid
     float *ema = nullptr, *ema_img = nullptr;
@@ -164,12 +166,9 @@ void timed_end(npm_ctx *ctx, int token, hipStream_t s);
 
 // common kernels (k_common.hip)
 hipError_t launch_init_params(npm_ctx *ctx, hipStream_t s);
-// packs the MLP images of the parameters (and of their average when kept)
-hipError_t launch_pack_mlp(npm_ctx *ctx, hipStream_t s);
 // repacks the images and rewrites the FP16 grids from the FP32 masters
 hipError_t launch_refresh_lowp(npm_ctx *ctx, hipStream_t s);
 hipError_t launch_adam(npm_ctx *ctx, float *grad, double *gradnorm_out, hipStream_t s);
-hipError_t launch_reduce_partials(npm_ctx *ctx, int nparts, double *out, hipStream_t s);
 hipError_t launch_reduce_scaled(const double *part, int nparts, double scale, double *out,
                                 hipStream_t s);
 hipError_t launch_fill_f32(float *p, int64_t n, float v, hipStream_t s);
@@ -306,11 +305,13 @@ hipError_t fused_query(npm_ctx *ctx, int64_t n, const float *pos, const float *a
                        float *sel = nullptr, void *feat = nullptr);
 // perm (optional): the order in which to visit the vertices; dg_tiles: the
 // per-tile dG buffer (required when grad is set); bins (optional): the levels
-// to scatter through the binned pass, with the context's bin buffers
+// to scatter through the binned pass, with the context's bin buffers; feat
+// (optional, with grad): feat_words(net, n) words for the grid features, then
+// encoded level by level for the tile kernel that reads them (k_train.hip)
 hipError_t fused_backward(npm_ctx *ctx, int64_t n, const float *pos, const float *aux,
                           const float *dir, const float *rad, const float *spdf, float *grad,
                           double *loss_out, const uint32_t *perm, const float *rec,
                           float *dg_tiles, const BinDesc *bins, hipStream_t s,
-                          const float *bsdf = nullptr);
+                          const float *bsdf = nullptr, void *feat = nullptr);
 
 }  // namespace npm

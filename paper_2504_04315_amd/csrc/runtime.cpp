@@ -187,7 +187,8 @@ npm_status npm::describe(const npm_config *cfg, Net *net, std::string *err)
     m.rm_elems = ro;
     const int64_t img = m.fwd_elems + m.bwd_elems;
     const int64_t lowp_grid = c.precision == NPM_PREC_BF16 ? 2 * L.grid_params : 0;
-    L.device_bytes = 16 * L.n_params + 6 * img + 4 * m.rm_elems + (int64_t)kPartials * 8 + 64 + lowp_grid +
+    const int64_t split = c.precision == NPM_PREC_FP32 ? 4 * m.bwd_elems : 0;
+    L.device_bytes = 16 * L.n_params + 6 * img + 4 * m.rm_elems + split + (int64_t)kPartials * 8 + 64 + lowp_grid +
                      (c.ema_decay > 0.0f ? 4 * L.n_params + 6 * img + lowp_grid : 0);
     if (c.exec_mode == NPM_EXEC_FUSED && c.learn_selection && !fused_shape_supported(n))
         return bad("no fused kernels with the selection output for this network shape (fused: "
@@ -315,6 +316,7 @@ static void free_ctx(npm_ctx *ctx)
     free_scratch(ctx);
     for (void *p : {(void *)ctx->params, (void *)ctx->grads, (void *)ctx->adam_m,
                     (void *)ctx->adam_v, ctx->grid16, (void *)ctx->mlp_img, ctx->mlp_img16,
+                    ctx->mlp_split,
                     (void *)ctx->partials, (void *)ctx->stats, (void *)ctx->s_dw_part,
                     (void *)ctx->s_perm, (void *)ctx->s_inv, (void *)ctx->s_rec,
                     (void *)ctx->s_qstage, (void *)ctx->s_feat,
@@ -368,12 +370,13 @@ npm_status npm_create(const npm_config *cfg, npm_ctx **out)
     alloc((void **)&ctx->adam_v, np * 4);
     alloc((void **)&ctx->mlp_img, (img + net.mlp.rm_elems) * 4);
     alloc((void **)&ctx->mlp_img16, img * 2);
+    if (net.cfg.precision == NPM_PREC_FP32) alloc(&ctx->mlp_split, net.mlp.bwd_elems * 4);
     alloc((void **)&ctx->partials, kPartials * 8);
     alloc((void **)&ctx->stats, 64);
-    // weight-gradient partials: 256 blocks x one layer (staged) or 1024 waves x
-    // all MLP weights (fused)
+    // weight-gradient partials: 256 blocks x one layer (staged) or x all MLP
+    // weights (fused)
     const int64_t mlp_w = np - net.lay.grid_params;
-    alloc((void **)&ctx->s_dw_part, std::max<int64_t>(256 * max_layer, 1024 * mlp_w) * 4);
+    alloc((void **)&ctx->s_dw_part, 256 * std::max<int64_t>(max_layer, mlp_w) * 4);
     if (net.cfg.precision == NPM_PREC_BF16) alloc(&ctx->grid16, net.lay.grid_params * 2);
     if (net.cfg.ema_decay > 0.0f) {
         alloc((void **)&ctx->ema, np * 4);
@@ -554,6 +557,14 @@ static bool use_feat(const npm_ctx *ctx, int64_t n)
            n > (bf ? kFeatQuery16 : kFeatQuery32);
 }
 
+// Whether a training batch's features are encoded level by level for the tile
+// kernel of k_train.hip: every fused shape but the FP32 form of the wide
+// NPM-product input, whose weight images and planes exceed the LDS.
+static bool train_feat(const npm_ctx *ctx)
+{
+    return ctx->net.mlp.in_p <= 32 || ctx->net.cfg.precision == NPM_PREC_BF16;
+}
+
 static hipError_t ensure_feat(npm_ctx *ctx, int64_t n)
 {
     const size_t words = feat_words(ctx->net, n);
@@ -673,9 +684,14 @@ static npm_status backward_impl(npm_ctx *ctx, int64_t n, const float *pos, const
         BinDesc bins;
         const bool binned = grad && use_bins(ctx, n, perm != nullptr, &bins);
         if (binned) NPM_HIP(ensure_bins(ctx, bins), "bin scratch allocation");
+        void *feat = nullptr;
+        if (grad && train_feat(ctx)) {
+            NPM_HIP(ensure_feat(ctx, n), "feature scratch allocation");
+            feat = ctx->s_feat;
+        }
         NPM_HIP(fused_backward(ctx, n, pos, aux, dir, rad, spdf, grad, loss_out, perm,
                                perm ? ctx->s_rec : nullptr, grad ? ctx->s_dgt : nullptr,
-                               binned ? &bins : nullptr, s, bsdf),
+                               binned ? &bins : nullptr, s, bsdf, feat),
                 "fused backward");
         return NPM_OK;
     }
