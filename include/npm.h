@@ -86,7 +86,7 @@ enum { NPM_ORDER_AUTO = 0, NPM_ORDER_NONE = 1, NPM_ORDER_SPATIAL = 2 };
 /* How the fused training path adds the gradient into the grid's hashed
  * levels (Sec. 4.2 gradient through the interpolation of Sec. 5.1).
  * NPM_SCATTER_ATOMIC adds each corner's contribution with an FP32 atomic
- * (through a tile's LDS window where its corners fall together);
+ * (after a sum in LDS where the corners of neighbours share a line);
  * NPM_SCATTER_BINNED first bins the contributions of the hashed levels by
  * table slice and sums each slice in one block (in FP64, or in 64-bit fixed
  * point in the precision form; rounded once to FP32), then adds it to the

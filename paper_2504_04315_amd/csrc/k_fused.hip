@@ -311,68 +311,6 @@ __global__ __launch_bounds__(64 * WV) void k_backward_fused(FusedArgs a, int mlp
     }
 }
 
-// Aggregated grid scatter of the per-tile dG (stride `rows` rows of 32 per
-// tile) in the same visiting order.  A wave takes a contiguous run of tiles;
-// per tile it stages the n_levels * F dG rows in LDS, takes the tile's
-// bounding box and scatters with the LDS window (scatter_tile).  Kept apart
-// from the MLP kernel: the atomics are bound by the rate of line requests
-// the memory system accepts, and at the one wave per SIMD the MLP kernel's
-// registers allow, a wave waiting on its atomics leaves its SIMD idle, while
-// this kernel runs four waves per SIMD.
-// per wave: 32 dG rows, then the window of kScatterWinRows rows holding the
-// sums -- FP64 (LDS FP64 atomic adds run several times faster than FP32 ones
-// on this chip), or 32-bit fixed point in the precision form (WT = int, no
-// FP64): kScatterWinRows * kStride / (2 F) lattice points
-constexpr int kScatterWinRows = 32;
-constexpr int kScatterRows = 32 + kScatterWinRows;
-
-template <int F, typename WT>
-__global__ __launch_bounds__(256) void k_scatter_tiles(GridDesc g, int64_t n,
-                                                       const float *__restrict__ pos,
-                                                       const uint32_t *perm,
-                                                       const float *__restrict__ rec,
-                                                       int rec_stride,
-                                                       const float *__restrict__ dgt, int rows,
-                                                       float *__restrict__ grad, uint32_t skip_mask)
-{
-    __shared__ uint32_t s_off[NPM_MAX_LEVELS];
-    __shared__ int s_res[NPM_MAX_LEVELS];
-    __shared__ __attribute__((aligned(16))) float buf[4 * kScatterRows * kStride];
-    stage_levels(g, s_off, s_res);
-    __syncthreads();
-    const GridView gv = grid_view(g, s_off, s_res, nullptr, nullptr);
-    constexpr int WIN_PTS = kScatterWinRows * kStride / (2 * F);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    float *tb = buf + wave * kScatterRows * kStride;
-    const int lr = g.n_levels * g.feat;           // dG rows the scatter reads (<= 32)
-    const int64_t ntiles = (n + 31) / 32;
-    const int64_t nwaves = (int64_t)gridDim.x * 4;
-    const int64_t gwave = blockIdx.x * (int64_t)4 + wave;
-    const int64_t per = (ntiles + nwaves - 1) / nwaves;
-    const int64_t t_end = (gwave + 1) * per < ntiles ? (gwave + 1) * per : ntiles;
-    for (int64_t t = gwave * per; t < t_end; ++t) {
-        const int64_t v = t * 32 + (lane & 31);
-        float lo[3], hi[3];
-        if (rec) {
-            const f32x4 a = *reinterpret_cast<const f32x4 *>(rec + (size_t)(v < n ? v : n - 1) * rec_stride);
-            tile_bbox(a[0], a[1], a[2], lo, hi);
-        } else {
-            const int64_t vv = visit(perm, v < n ? v : n - 1);
-            tile_bbox(pos[vv], pos[n + vv], pos[2 * n + vv], lo, hi);
-        }
-        const float *src = dgt + (size_t)t * rows * 32;
-        for (int i = lane; i < lr * 8; i += 64) {
-            const f32x4 q = reinterpret_cast<const f32x4 *>(src)[i];
-            *reinterpret_cast<f32x4 *>(tb + (i >> 3) * kStride + (i & 7) * 4) = q;
-        }
-        wave_lds_fence();
-        scatter_tile<F, WIN_PTS, WT>(gv, tb, pos, perm, n, t, lane, grad, lo, hi,
-                                     reinterpret_cast<WT *>(tb + 32 * kStride), rec, rec_stride,
-                                     skip_mask);
-        wave_lds_fence();
-    }
-}
-
 // Sum of the blocks' weight-gradient partials into the gradient: a block of
 // 256 threads covers 16 weights, its 16 thread rows a sixteenth of the
 // partials each (several loads in flight per thread, 768 blocks at the
@@ -502,14 +440,12 @@ hipError_t fused_backward(npm_ctx *ctx, int64_t n, const float *pos, const float
     if (e != hipSuccess) return e;
     const int blocks = train_blocks(n);
     if (grad) {
-        const int64_t tiles = (n + 31) / 32;
-        const int64_t waves = std::min<int64_t>(tiles, 4096);
         const int rows = std::max(ctx->net.mlp.in_p, 32);
         uint32_t skip = 0u;
         if (bins)
             for (int j = 0; j < bins->nb; ++j) skip |= 1u << bins->lv[j];
         const uint32_t all = ctx->net.grid.n_levels >= 32 ? ~0u : (1u << ctx->net.grid.n_levels) - 1u;
-        // The windowed scatter and the weight-gradient sum write other parts
+        // The chunked scatter and the weight-gradient sum write other parts
         // of the gradient than the binned scatter and read only the per-tile
         // dG: with bins they run on the side stream, beside the binned passes
         // (which leave CUs idle in their scan and in the reduce's last wave of
@@ -523,19 +459,9 @@ hipError_t fused_backward(npm_ctx *ctx, int64_t n, const float *pos, const float
         }
         if (skip != all) {
             timed_begin(ctx, "fused_scatter", s2, &tok);
-            const bool fixed = ctx->net.cfg.precision == NPM_PREC_BF16;
-            const dim3 grid((unsigned)((waves + 3) / 4)), block(256);
-#define NPM_SCATTER_LAUNCH(FV, WT)                                                                 \
-    hipLaunchKernelGGL((k_scatter_tiles<FV, WT>), grid, block, 0, s2, ctx->net.grid, n, pos, perm, \
-                       rec, a.rec_stride, dg_tiles, rows, grad, skip)
-            switch (ctx->net.grid.feat) {
-            case 1: if (fixed) NPM_SCATTER_LAUNCH(1, int); else NPM_SCATTER_LAUNCH(1, double); break;
-            case 2: if (fixed) NPM_SCATTER_LAUNCH(2, int); else NPM_SCATTER_LAUNCH(2, double); break;
-            default: if (fixed) NPM_SCATTER_LAUNCH(4, int); else NPM_SCATTER_LAUNCH(4, double); break;
-            }
-#undef NPM_SCATTER_LAUNCH
+            e = chunk_scatter(ctx->net, n, pos, perm, rec, a.rec_stride, dg_tiles, rows, grad,
+                              all & ~skip, s2);
             timed_end(ctx, tok, s2);
-            e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
         const int count = (int)(ctx->net.lay.n_params - ctx->net.lay.grid_params);

@@ -114,7 +114,7 @@ struct npm_ctx {
     // (and the scan's block totals), and the binned items
     uint32_t *s_bin_cnt = nullptr, *s_bin_items = nullptr;
     size_t bin_cnt_words = 0, bin_item_words = 0;
-    // a second stream (default priority) on which the windowed scatter and
+    // a second stream (default priority) on which the chunked scatter and
     // the weight-gradient sum run beside the binned scatter, forked from and
     // joined back to the caller's stream by the two events
     hipStream_t side = nullptr;
@@ -219,10 +219,9 @@ hipError_t spatial_order(npm_ctx *ctx, int64_t n, const float *pos, const float 
                          const float *dir, const float *rad, const float *spdf, uint32_t *perm,
                          uint32_t *inv, float *rec, uint32_t *cells, hipStream_t s);
 // Smallest batch NPM_ORDER_AUTO sorts.  On the 16-level hash grid at 2^20
-// vertices the sort (0.22 ms) halves the scatter's line requests through the
-// LDS window (4.43 -> 2.42 ms) and speeds the tile kernel's gathers (1.61 ->
-// 1.28 ms); a batch of 2^15 vertices is still dense enough for the window to
-// cover the coarse levels.
+// vertices the sort (0.12 ms) lets the scatter sum shared corners and lines in
+// LDS and speeds the encode's gathers (475 -> 262 us with a thread per vertex);
+// a batch of 2^15 vertices is still dense enough to share the coarse levels'.
 constexpr int64_t kSortMinBatch = 1 << 15;
 // 32-bit words of the sort's cell scratch: 2^18 cell counters, then 256
 // block totals of its scan.
@@ -246,10 +245,12 @@ constexpr int64_t kBinMinBatch = 1 << 15;
 // ... and only grids whose binned levels split into this many slices (small
 // tables leave the reduce too few blocks).
 constexpr int kBinMinBins = 256;
-// In a spatially ordered batch the hashed levels with D_l below this mostly
-// fit the tile's LDS window and stay with the windowed scatter (on the
-// 16-level production grid binning from D_l >= 100 on beats binning every
-// hashed level: 1.01 against 1.05 ms per 2^20-vertex batch).
+// In a spatially ordered batch the hashed levels with D_l below this share
+// enough lines to stay with the chunked scatter.  Training step of the
+// 16-level production grid with the line at 100 / 140 / 180 / 250: 2^20
+// vertices FP32 1.68 / 1.61 / 1.63 / 1.66 ms, precision form 1.18 / 1.15 /
+// 1.18 / 1.19; 300,001 vertices 545 / 564 / 580 / 622 us; 100,003 vertices 470
+// / 473 / 484 / 499: sparser batches share fewer lines.
 constexpr int kBinMinResOrdered = 100;
 struct BinDesc {
     int32_t nb;                        // binned levels
@@ -271,6 +272,13 @@ hipError_t binned_scatter(npm_ctx *ctx, const BinDesc &b, int64_t n, const float
                           const uint32_t *perm, const float *rec, int rec_stride,
                           const float *dgt, int rows, float *grad, uint32_t *cnt,
                           uint32_t *items, hipStream_t s);
+
+// Grid scatter of the levels of level_mask (k_scatter.hip): chunks of the
+// visiting order summed line by line in LDS, then one FP32 atomic per touched
+// float.  dgt/rows: as above.
+hipError_t chunk_scatter(const Net &net, int64_t n, const float *pos, const uint32_t *perm,
+                         const float *rec, int rec_stride, const float *dgt, int rows,
+                         float *grad, uint32_t level_mask, hipStream_t s);
 
 // fused path (k_query.hip, k_fused.hip)
 // whether the fused kernels are instantiated for the network's shape (the
