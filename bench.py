@@ -74,14 +74,12 @@ WORK = {
 L_BINNED, L_WINDOW, T_HASH = 10, 6, 1 << 19
 BIN_ITEM_B = 16
 BIN_ITEMS_B = L_BINNED * 4 * BIN_ITEM_B           # 640 B per vertex
-BIN_COUNTERS_B = 4 * 640 / 1024                   # one counter per bin and chunk
+BIN_COUNTERS_B = 8 * 640 / 1024                   # offset and count per bin and chunk
 BIN_WORK = {
     # positions, dG of the binned levels; counters written
     "bin_count": dict(bytes=16 + L_BINNED * 2 * 4 + BIN_COUNTERS_B, flops=0),
-    # two read + write passes over the counters
-    "bin_scan": dict(bytes=4 * BIN_COUNTERS_B, flops=0),
-    # positions, dG, the chunk's counter pairs, items written
-    "bin_place": dict(bytes=16 + L_BINNED * 2 * 4 + 2 * BIN_COUNTERS_B + BIN_ITEMS_B, flops=0),
+    # positions, dG, the chunk's runs, items written
+    "bin_place": dict(bytes=16 + L_BINNED * 2 * 4 + BIN_COUNTERS_B + BIN_ITEMS_B, flops=0),
     # items read; the hashed tables' gradient read and written once per batch
     # (its per-vertex share at 2^20 vertices is added in main)
     "bin_reduce": dict(bytes=BIN_ITEMS_B, flops=0),

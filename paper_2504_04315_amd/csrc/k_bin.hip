@@ -15,11 +15,11 @@
 // (1 - f) times them to the lower entry and f times them to the upper one.
 //
 //   count   per chunk of kBinChunk visiting slots, the number of items of
-//           every (level, slice) bin              -> cnt[bin][chunk]
-//   scan    exclusive prefix sum of cnt in bin-major order: the chunk's run
-//           of items inside its bin's contiguous range
+//           every (level, slice) bin; the chunk's run of each bin follows the
+//           runs counted before it (one add to the bin's total)
 //   place   the chunk's items, ordered by bin in LDS and written out as
-//           contiguous runs of (key, fraction, F values) records
+//           contiguous runs of (key, fraction, F values) records, the bins one
+//           after the other in the item buffer
 //   reduce  one block per bin: LDS accumulation of its items -- FP64, or in
 //           the precision form 64-bit fixed point (no FP64) -- then one
 //           coalesced read-add-write of the slice into the gradient
@@ -101,6 +101,50 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x, int lane)
 
 }  // namespace
 
+// The binned levels j0 .. j1 - 1 of a block's share (blockIdx.y of gridDim.y).
+__device__ __forceinline__ void level_share(int nb, int &j0, int &j1)
+{
+    j0 = nb * (int)blockIdx.y / (int)gridDim.y;
+    j1 = nb * ((int)blockIdx.y + 1) / (int)gridDim.y;
+}
+
+// Exclusive prefix sum of the m <= 2 kBinChunk words of v into out (LDS), by a
+// block of kBinChunk threads; wsum: 16 words of LDS.
+__device__ __forceinline__ void block_exclusive_scan(const uint32_t *__restrict__ v, int m,
+                                                     uint32_t *out, uint32_t *wsum)
+{
+    static_assert(kBinMaxBins <= 2 * kBinChunk && kBinChunk == 1024, "two bins a thread, 16 waves");
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const uint32_t x0 = 2 * t < m ? v[2 * t] : 0u, x1 = 2 * t + 1 < m ? v[2 * t + 1] : 0u;
+    const uint32_t inc = wave_inclusive_scan(x0 + x1, lane);
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    if (wave == 0) {
+        const uint32_t ws = lane < 16 ? wsum[lane] : 0u;
+        const uint32_t wi = wave_inclusive_scan(ws, lane);
+        if (lane < 16) wsum[lane] = wi - ws;
+    }
+    __syncthreads();
+    const uint32_t e = wsum[wave] + inc - x0 - x1;
+    if (2 * t < m) out[2 * t] = e;
+    if (2 * t + 1 < m) out[2 * t + 1] = e + x0;
+}
+
+// Clears the bins' totals and the batch's largest |dG| after them.
+__global__ void k_bin_zero(uint32_t *__restrict__ tot, int words)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < words) tot[i] = 0u;
+}
+
+// Bound by the LDS counts and the reads of position and dG.  The offsets come
+// from one add per chunk and bin to the bin's total (0.65 M at 2^20 vertices, a
+// few microseconds), which replaced three passes over chunk-major counters
+// (16 us together, 25 more where another stream's blocks held the CUs); a
+// chunk's runs lie together, one line request for 16 of them.
+//
+// Per chunk: {offset within the bin, items} of every bin into run[chunk][bin],
+// and the largest |dG| into tot[nbins], which scales the fixed-point reduce.
 template <int F>
 __global__ __launch_bounds__(kBinChunk) void k_bin_count(GridDesc g, BinDesc bd, int64_t n,
                                                          const float *__restrict__ pos,
@@ -108,8 +152,8 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_count(GridDesc g, BinDesc bd,
                                                          const float *__restrict__ rec,
                                                          int rec_stride,
                                                          const float *__restrict__ dgt, int rows,
-                                                         uint32_t *__restrict__ cnt,
-                                                         uint32_t *__restrict__ cmax)
+                                                         uint2 *__restrict__ run,
+                                                         uint32_t *__restrict__ tot)
 {
     // NC copies of the histogram, lane t counting in copy t mod NC: fewer lanes of
     // one instruction on one counter (the copies sit HS words apart, off each
@@ -119,14 +163,17 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_count(GridDesc g, BinDesc bd,
     __shared__ uint32_t hist[NC * HS];
     __shared__ int s_lv[NPM_MAX_LEVELS], s_res[NPM_MAX_LEVELS];
     __shared__ uint32_t s_max;
-    for (int k = threadIdx.x; k < NC * HS; k += kBinChunk) hist[k] = 0u;
+    int j0, j1;
+    level_share(bd.nb, j0, j1);
+    const int k0 = j0 * bd.ns, nk = (j1 - j0) * bd.ns;
+    for (int k = threadIdx.x; k < nk; k += kBinChunk)
+#pragma unroll
+        for (int r = 0; r < NC; ++r) hist[r * HS + k] = 0u;
     if (threadIdx.x == 0) s_max = 0u;
     if (threadIdx.x < NPM_MAX_LEVELS) {
         s_lv[threadIdx.x] = bd.lv[threadIdx.x];
         s_res[threadIdx.x] = g.res[threadIdx.x];
     }
-    // the sentinel after the last bin: the scan turns it into the total
-    if (blockIdx.x == 0 && threadIdx.x == 0) cnt[(size_t)bd.nbins * bd.n_chunks] = 0u;
     __syncthreads();
     const int64_t s = blockIdx.x * (int64_t)kBinChunk + threadIdx.x;
     uint32_t *hc = hist + (threadIdx.x & (NC - 1)) * HS;
@@ -135,12 +182,12 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_count(GridDesc g, BinDesc bd,
         float p[3];
         slot_position(pos, perm, rec, rec_stride, n, s, p);
         float dn[F];
-        slot_dg<F>(dgt, rows, s, s_lv[0], dn);
-        for (int j = 0; j < bd.nb; ++j) {
+        slot_dg<F>(dgt, rows, s, s_lv[j0], dn);
+        for (int j = j0; j < j1; ++j) {
             const int l = s_lv[j];
             float d[F];
             const bool any = take_dg<F>(dn, d);
-            if (j + 1 < bd.nb) slot_dg<F>(dgt, rows, s, s_lv[j + 1], dn);
+            if (j + 1 < j1) slot_dg<F>(dgt, rows, s, s_lv[j + 1], dn);
             if (!any) continue;
 #pragma unroll
             for (int f = 0; f < F; ++f) dmax = fmaxf(dmax, fabsf(d[f]));
@@ -153,87 +200,21 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_count(GridDesc g, BinDesc bd,
                 uint32_t m;
                 float wyz;
                 const uint32_t slot = pair_slot(c, fr, pr, g.table_mask, m, wyz);
-                atomicAdd(&hc[j * bd.ns + (int)(slot >> bd.log2s)], 1u);
+                atomicAdd(&hc[(j - j0) * bd.ns + (int)(slot >> bd.log2s)], 1u);
             }
         }
     }
     // non-negative floats order as their bit patterns
     atomicMax(&s_max, __float_as_uint(dmax));
     __syncthreads();
-    for (int k = threadIdx.x; k < bd.nbins; k += kBinChunk) {
+    for (int k = threadIdx.x; k < nk; k += kBinChunk) {
         uint32_t c = 0u;
 #pragma unroll
         for (int r = 0; r < NC; ++r) c += hist[r * HS + k];
-        cnt[(size_t)k * bd.n_chunks + blockIdx.x] = c;
+        const uint32_t o = c ? atomicAdd(&tot[k0 + k], c) : 0u;
+        run[(size_t)blockIdx.x * bd.nbins + k0 + k] = make_uint2(o, c);
     }
-    if (threadIdx.x == 0) cmax[blockIdx.x] = s_max;
-}
-
-// Exclusive prefix sum of m counters: per block of 1024, then over the block
-// totals (one block, in segments), then the totals added back.
-__global__ __launch_bounds__(1024) void k_bin_scan_local(uint32_t *__restrict__ v, int64_t m,
-                                                         uint32_t *__restrict__ totals)
-{
-    __shared__ uint32_t wsum[16];
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int64_t i = blockIdx.x * (int64_t)1024 + t;
-    const uint32_t x = i < m ? v[i] : 0u;
-    const uint32_t inc = wave_inclusive_scan(x, lane);
-    if (lane == 63) wsum[wave] = inc;
-    __syncthreads();
-    if (wave == 0) {
-        const uint32_t ws = lane < 16 ? wsum[lane] : 0u;
-        const uint32_t wi = wave_inclusive_scan(ws, lane);
-        if (lane < 16) wsum[lane] = wi - ws;
-        if (lane == 15) totals[blockIdx.x] = wi;
-    }
-    __syncthreads();
-    if (i < m) v[i] = wsum[wave] + inc - x;
-}
-
-// (The same single block also reduces the chunks' largest |dG| to the
-// batch's, cmax[n_chunks], which scales the fixed-point reduce.)
-__global__ __launch_bounds__(1024) void k_bin_scan_totals(uint32_t *__restrict__ totals, int nblk,
-                                                          uint32_t *__restrict__ cmax,
-                                                          int64_t n_chunks)
-{
-    __shared__ uint32_t wsum[16];
-    __shared__ uint32_t carry, bmax;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    if (t == 0) {
-        carry = 0u;
-        bmax = 0u;
-    }
-    __syncthreads();
-    uint32_t mx = 0u;
-    for (int64_t i = t; i < n_chunks; i += 1024) mx = max(mx, cmax[i]);
-    atomicMax(&bmax, mx);
-    for (int base = 0; base < nblk; base += 1024) {
-        const int i = base + t;
-        const uint32_t x = i < nblk ? totals[i] : 0u;
-        const uint32_t inc = wave_inclusive_scan(x, lane);
-        if (lane == 63) wsum[wave] = inc;
-        __syncthreads();
-        if (wave == 0) {
-            const uint32_t ws = lane < 16 ? wsum[lane] : 0u;
-            const uint32_t wi = wave_inclusive_scan(ws, lane);
-            if (lane < 16) wsum[lane] = wi - ws;
-        }
-        __syncthreads();
-        const uint32_t c = carry;
-        if (i < nblk) totals[i] = c + wsum[wave] + inc - x;
-        __syncthreads();
-        if (t == 1023) carry = c + wsum[15] + inc;
-        __syncthreads();
-    }
-    if (t == 0) cmax[n_chunks] = bmax;
-}
-
-__global__ __launch_bounds__(1024) void k_bin_scan_add(uint32_t *__restrict__ v, int64_t m,
-                                                       const uint32_t *__restrict__ totals)
-{
-    const int64_t i = blockIdx.x * (int64_t)1024 + threadIdx.x;
-    if (i < m) v[i] += totals[blockIdx.x];
+    if (threadIdx.x == 0 && s_max) atomicMax(&tot[bd.nbins], s_max);
 }
 
 template <int F>
@@ -243,7 +224,9 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_place(GridDesc g, BinDesc bd,
                                                          const float *__restrict__ rec,
                                                          int rec_stride,
                                                          const float *__restrict__ dgt, int rows,
-                                                         const uint32_t *__restrict__ off,
+                                                         const uint2 *__restrict__ run,
+                                                         const uint32_t *__restrict__ tot,
+                                                         uint32_t *__restrict__ base,
                                                          uint32_t *__restrict__ items)
 {
     constexpr int W = 2 + F;                 // words per item: key, fraction, F values
@@ -251,6 +234,7 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_place(GridDesc g, BinDesc bd,
     __shared__ __attribute__((aligned(16))) uint32_t st[CAP * W];
     __shared__ uint16_t sb[CAP];
     __shared__ int s_lv[NPM_MAX_LEVELS], s_res[NPM_MAX_LEVELS];
+    __shared__ uint32_t wsum[16];
     // sized by the launch: each bin's run start and length, then the level's
     // local bases and ranks (bin_place_lds_bytes)
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
@@ -261,12 +245,19 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_place(GridDesc g, BinDesc bd,
         s_res[t] = g.res[t];
     }
     const int64_t chunk = blockIdx.x;
-    // this chunk's run of every bin (start, length), all fetched at once
-    for (int kk = t; kk < bd.nbins; kk += kBinChunk) {
-        const size_t idx = (size_t)kk * bd.n_chunks + chunk;
-        const uint32_t g0 = off[idx];
-        gd[kk] = g0;
-        cn[kk] = off[idx + 1] - g0;
+    int j0, j1;
+    level_share(bd.nb, j0, j1);
+    // this chunk's run of every bin of its levels (start, length)
+    block_exclusive_scan(tot, bd.nbins, gd, wsum);
+    __syncthreads();
+    if (blockIdx.x == 0 && blockIdx.y == 0) {          // for the reduce
+        for (int kk = t; kk < bd.nbins; kk += kBinChunk) base[kk] = gd[kk];
+        __syncthreads();
+    }
+    for (int kk = j0 * bd.ns + t; kk < j1 * bd.ns; kk += kBinChunk) {
+        const uint2 r = run[(size_t)chunk * bd.nbins + kk];
+        gd[kk] += r.x;
+        cn[kk] = r.y;
     }
     const int64_t s = chunk * kBinChunk + t;
     const bool live = s < n;
@@ -277,8 +268,8 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_place(GridDesc g, BinDesc bd,
     float dn[F];
 #pragma unroll
     for (int f = 0; f < F; ++f) dn[f] = 0.0f;
-    if (live) slot_dg<F>(dgt, rows, s, s_lv[0], dn);
-    for (int j = 0; j < bd.nb; ++j) {
+    if (live) slot_dg<F>(dgt, rows, s, s_lv[j0], dn);
+    for (int j = j0; j < j1; ++j) {
         // local base of the chunk's run of each bin of the level
         if (t < 64) {
             uint32_t c0 = 0u;
@@ -299,7 +290,7 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_place(GridDesc g, BinDesc bd,
         const int l = s_lv[j];
         float d[F];
         const bool any = take_dg<F>(dn, d);
-        if (live && j + 1 < bd.nb) slot_dg<F>(dgt, rows, s, s_lv[j + 1], dn);
+        if (live && j + 1 < j1) slot_dg<F>(dgt, rows, s, s_lv[j + 1], dn);
         if (live && any) {
             int c[3];
             float fr[3];
@@ -372,9 +363,9 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_place(GridDesc g, BinDesc bd,
 // 640 blocks making two and a half rounds of the chip).
 template <int F, bool FIXED>
 __global__ __launch_bounds__(kBinReduceThreads) void k_bin_reduce(GridDesc g, BinDesc bd,
-                                                                  const uint32_t *__restrict__ off,
+                                                                  const uint32_t *__restrict__ tot,
+                                                                  const uint32_t *__restrict__ base,
                                                                   const uint32_t *__restrict__ items,
-                                                                  const uint32_t *__restrict__ bmax,
                                                                   float *__restrict__ grad)
 {
     constexpr int NT = kBinReduceThreads, U = kBinReduceBatch;
@@ -384,11 +375,11 @@ __global__ __launch_bounds__(kBinReduceThreads) void k_bin_reduce(GridDesc g, Bi
     const int k = blockIdx.x, j = k / bd.ns, slice = k - j * bd.ns;
     const uint32_t S = 1u << bd.log2s;
     const int nf = (int)S * F;
-    const uint64_t beg = off[(size_t)k * bd.n_chunks];
-    const uint64_t end = min(off[(size_t)(k + 1) * bd.n_chunks], (uint32_t)bd.cap);
+    const uint64_t beg = base[k];
+    const uint64_t end = min(beg + tot[k], (uint64_t)bd.cap);
     int kx = 0;                                  // fixed point: the scale is 2^kx
     if constexpr (FIXED) {
-        const float M = __uint_as_float(*bmax);
+        const float M = __uint_as_float(tot[bd.nbins]);
         if (!(M > 0.0f) || end <= beg) return;   // nothing to add (block-uniform)
         int e;
         frexpf(M, &e);                           // M < 2^e
@@ -512,12 +503,14 @@ bool bin_plan(const npm_ctx *ctx, int64_t n, bool ordered, BinDesc *out)
     return true;
 }
 
-// counters (bin-major, and the sentinel), the scan's block totals, then the
-// chunks' largest |dG| and the batch's
+// the bins' totals and the batch's largest |dG| (bin_clear_words, zero before
+// the pass), the bins' starts, then the chunks' runs (two words per bin and chunk)
+int bin_clear_words(const BinDesc &b) { return b.nbins + 1; }
+
 size_t bin_count_words(const BinDesc &b)
 {
-    const int64_t m = (int64_t)b.nbins * b.n_chunks + 1;
-    return (size_t)m + (size_t)((m + 1023) / 1024) + (size_t)b.n_chunks + 1;
+    const size_t head = (2 * (size_t)b.nbins + 2) / 2 * 2;
+    return head + 2 * (size_t)b.nbins * (size_t)b.n_chunks;
 }
 
 // items: cap records of (key, x fraction, F FP32 values)
@@ -532,32 +525,34 @@ static void launch_bins(const GridDesc &g, const BinDesc &b, int64_t n, const fl
                         int rows, float *grad, uint32_t *cnt, uint32_t *items, int phase,
                         bool fixed, hipStream_t s)
 {
-    const int64_t m = (int64_t)b.nbins * b.n_chunks + 1;
-    const int nblk = (int)((m + 1023) / 1024);
-    uint32_t *cmax = cnt + m + nblk;             // n_chunks + 1 words
+    uint32_t *tot = cnt, *base = cnt + b.nbins + 1;
+    uint2 *run = reinterpret_cast<uint2 *>(cnt + (2 * (size_t)b.nbins + 2) / 2 * 2);
+    // a chunk's levels go to one block, or are shared by several where the
+    // chunks alone are fewer than two blocks a CU (32,771 vertices, 12 levels:
+    // place 37 -> 10 us; 100,003 vertices, 10 levels: 36 -> 26)
+    const int gy = (int)std::min<int64_t>(b.nb, (511 + b.n_chunks) / b.n_chunks);
+    const dim3 grid((unsigned)b.n_chunks, (unsigned)gy);
     switch (phase) {
     case 0:
-        hipLaunchKernelGGL(k_bin_count<F>, dim3((unsigned)b.n_chunks), dim3(kBinChunk), 0, s, g, b,
-                           n, pos, perm, rec, rec_stride, dgt, rows, cnt, cmax);
+        hipLaunchKernelGGL(k_bin_zero, dim3((b.nbins + 256) / 256), dim3(256), 0, s, tot,
+                           bin_clear_words(b));
         break;
     case 1:
-        hipLaunchKernelGGL(k_bin_scan_local, dim3(nblk), dim3(1024), 0, s, cnt, m, cnt + m);
-        hipLaunchKernelGGL(k_bin_scan_totals, dim3(1), dim3(1024), 0, s, cnt + m, nblk, cmax,
-                           b.n_chunks);
-        hipLaunchKernelGGL(k_bin_scan_add, dim3(nblk), dim3(1024), 0, s, cnt, m, cnt + m);
+        hipLaunchKernelGGL(k_bin_count<F>, grid, dim3(kBinChunk), 0, s, g, b, n, pos, perm, rec,
+                           rec_stride, dgt, rows, run, tot);
         break;
     case 2:
-        hipLaunchKernelGGL(k_bin_place<F>, dim3((unsigned)b.n_chunks), dim3(kBinChunk),
+        hipLaunchKernelGGL(k_bin_place<F>, grid, dim3(kBinChunk),
                            (size_t)(2 * b.nbins + 2 * b.ns + 1) * 4, s, g, b, n, pos, perm, rec,
-                           rec_stride, dgt, rows, cnt, items);
+                           rec_stride, dgt, rows, run, tot, base, items);
         break;
     default:
         if (fixed)
             hipLaunchKernelGGL((k_bin_reduce<F, true>), dim3(b.nbins), dim3(kBinReduceThreads), 0, s,
-                               g, b, cnt, items, cmax + b.n_chunks, grad);
+                               g, b, tot, base, items, grad);
         else
             hipLaunchKernelGGL((k_bin_reduce<F, false>), dim3(b.nbins), dim3(kBinReduceThreads), 0, s,
-                               g, b, cnt, items, cmax + b.n_chunks, grad);
+                               g, b, tot, base, items, grad);
         break;
     }
 }
@@ -565,13 +560,13 @@ static void launch_bins(const GridDesc &g, const BinDesc &b, int64_t n, const fl
 hipError_t binned_scatter(npm_ctx *ctx, const BinDesc &b, int64_t n, const float *pos,
                           const uint32_t *perm, const float *rec, int rec_stride,
                           const float *dgt, int rows, float *grad, uint32_t *cnt,
-                          uint32_t *items, hipStream_t s)
+                          uint32_t *items, bool cleared, hipStream_t s)
 {
     const GridDesc &g = ctx->net.grid;
     // the precision form sums in fixed point (no FP64)
     const bool fx = ctx->net.cfg.precision == NPM_PREC_BF16;
-    static const char *names[4] = {"bin_count", "bin_scan", "bin_place", "bin_reduce"};
-    for (int phase = 0; phase < 4; ++phase) {
+    static const char *names[4] = {"bin_zero", "bin_count", "bin_place", "bin_reduce"};
+    for (int phase = cleared ? 1 : 0; phase < 4; ++phase) {
         int tok;
         timed_begin(ctx, names[phase], s, &tok);
         switch (g.feat) {

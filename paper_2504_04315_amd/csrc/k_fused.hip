@@ -477,7 +477,7 @@ hipError_t fused_backward(npm_ctx *ctx, int64_t n, const float *pos, const float
         if (e != hipSuccess) return e;
         if (bins) {
             e = binned_scatter(ctx, *bins, n, pos, perm, rec, a.rec_stride, dg_tiles, rows, grad,
-                               ctx->s_bin_cnt, ctx->s_bin_items, s);
+                               ctx->s_bin_cnt, ctx->s_bin_items, perm != nullptr, s);
             if (e == hipSuccess) e = hipEventRecord(ctx->ev_join, s2);
             if (e == hipSuccess) e = hipStreamWaitEvent(s, ctx->ev_join, 0);
             if (e != hipSuccess) return e;

@@ -34,8 +34,11 @@ __device__ __forceinline__ uint32_t sort_cell(const float *__restrict__ pos, int
     return spread3(c[0]) | (spread3(c[1]) << 1) | (spread3(c[2]) << 2);
 }
 
-__global__ void k_sort_zero(uint32_t *__restrict__ cnt)
+__global__ void k_sort_zero(uint32_t *__restrict__ cnt, uint32_t *__restrict__ clear,
+                            int clear_words)
 {
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < clear_words; i += gridDim.x * blockDim.x)
+        clear[i] = 0u;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kSortCells; i += gridDim.x * blockDim.x)
         cnt[i] = 0u;
 }
@@ -135,12 +138,14 @@ __global__ void k_sort_place(const float *__restrict__ pos, const float *__restr
 // 8 floats per slot (16 with aux)
 hipError_t spatial_order(npm_ctx *ctx, int64_t n, const float *pos, const float *aux,
                          const float *dir, const float *rad, const float *spdf, uint32_t *perm,
-                         uint32_t *inv, float *rec, uint32_t *cells, hipStream_t s)
+                         uint32_t *inv, float *rec, uint32_t *cells, hipStream_t s,
+                         uint32_t *clear, int clear_words)
 {
     int tok;
     timed_begin(ctx, "spatial_sort", s, &tok);
     const unsigned blocks = (unsigned)((n + 255) / 256);
-    hipLaunchKernelGGL(k_sort_zero, dim3(256), dim3(256), 0, s, cells);
+    hipLaunchKernelGGL(k_sort_zero, dim3(256), dim3(256), 0, s, cells, clear,
+                       clear_words);
     hipLaunchKernelGGL(k_sort_count, dim3(blocks), dim3(256), 0, s, pos, n, cells, inv);
     hipLaunchKernelGGL(k_sort_scan_local, dim3(kScanBlocks), dim3(1024), 0, s, cells,
                        cells + kSortCells);

@@ -214,10 +214,12 @@ hipError_t staged_scatter(npm_ctx *ctx, int64_t n, const float *pos, const float
                           float *grad, hipStream_t s);
 
 // spatial order of a batch (k_sort.hip): perm lists the vertices by cell,
-// inv (required, n entries) receives its inverse
+// inv (required, n entries) receives its inverse; clear: further words to zero
+// on the way (the bins' totals), or null
 hipError_t spatial_order(npm_ctx *ctx, int64_t n, const float *pos, const float *aux,
                          const float *dir, const float *rad, const float *spdf, uint32_t *perm,
-                         uint32_t *inv, float *rec, uint32_t *cells, hipStream_t s);
+                         uint32_t *inv, float *rec, uint32_t *cells, hipStream_t s,
+                         uint32_t *clear = nullptr, int clear_words = 0);
 // Smallest batch NPM_ORDER_AUTO sorts.  On the 16-level hash grid at 2^20
 // vertices the sort (0.12 ms) lets the scatter sum shared corners and lines in
 // LDS and speeds the encode's gathers (475 -> 262 us with a thread per vertex);
@@ -264,14 +266,16 @@ struct BinDesc {
 // false when the batch has no level to bin or exceeds the pass's limits
 bool bin_plan(const npm_ctx *ctx, int64_t n, bool ordered, BinDesc *out);
 size_t bin_count_words(const BinDesc &b);
+int bin_clear_words(const BinDesc &b);     // the first words of the counters
 size_t bin_item_words(const BinDesc &b, int feat);
 // dgt/rows: the per-tile dG of the batch in visiting order (perm / rec as
 // for the fused backward); cnt and items: bin_count_words and
-// bin_item_words 32-bit words
+// bin_item_words 32-bit words; cleared: the first bin_clear_words of cnt are
+// already zero
 hipError_t binned_scatter(npm_ctx *ctx, const BinDesc &b, int64_t n, const float *pos,
                           const uint32_t *perm, const float *rec, int rec_stride,
                           const float *dgt, int rows, float *grad, uint32_t *cnt,
-                          uint32_t *items, hipStream_t s);
+                          uint32_t *items, bool cleared, hipStream_t s);
 
 // Grid scatter of the levels of level_mask (k_scatter.hip): chunks of the
 // visiting order summed line by line in LDS, then one FP32 atomic per touched

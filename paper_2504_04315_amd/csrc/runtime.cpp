@@ -674,16 +674,18 @@ static npm_status backward_impl(npm_ctx *ctx, int64_t n, const float *pos, const
 {
     if (ctx->net.cfg.exec_mode == NPM_EXEC_FUSED) {
         const uint32_t *perm = nullptr;
-        if (grad && use_order(ctx, n)) {
-            NPM_HIP(ensure_sort(ctx, n), "order scratch allocation");
+        const bool ordered = grad && use_order(ctx, n);
+        BinDesc bins;
+        const bool binned = grad && use_bins(ctx, n, ordered, &bins);
+        if (ordered) NPM_HIP(ensure_sort(ctx, n), "order scratch allocation");
+        if (grad) NPM_HIP(ensure_dgt(ctx, n), "dG scratch allocation");
+        if (binned) NPM_HIP(ensure_bins(ctx, bins), "bin scratch allocation");
+        if (ordered) {
             NPM_HIP(spatial_order(ctx, n, pos, aux, dir, rad, spdf, ctx->s_perm, ctx->s_inv,
-                                  ctx->s_rec, ctx->s_cells, s), "spatial order");
+                                  ctx->s_rec, ctx->s_cells, s, binned ? ctx->s_bin_cnt : nullptr,
+                                  binned ? bin_clear_words(bins) : 0), "spatial order");
             perm = ctx->s_perm;
         }
-        if (grad) NPM_HIP(ensure_dgt(ctx, n), "dG scratch allocation");
-        BinDesc bins;
-        const bool binned = grad && use_bins(ctx, n, perm != nullptr, &bins);
-        if (binned) NPM_HIP(ensure_bins(ctx, bins), "bin scratch allocation");
         void *feat = nullptr;
         if (grad && train_feat(ctx)) {
             NPM_HIP(ensure_feat(ctx, n), "feature scratch allocation");
