@@ -241,12 +241,17 @@ constexpr int kBinReduceThreads = 1024;
 constexpr int kBinReduceBatch = 4;         // items in flight per thread
 constexpr int kBinMaxBins = 2048;
 constexpr int kBinMaxSlices = 1024;
-// Smallest batch NPM_SCATTER_AUTO bins (the count, scan, place and reduce
-// launches cost a few microseconds each).
-constexpr int64_t kBinMinBatch = 1 << 15;
+// Smallest batch NPM_SCATTER_AUTO bins (the count, place and reduce launches,
+// and the reduce's pass over every slice, whatever the batch).  Training step,
+// chunked scatter alone / binned: 2^17 entries, 6,001 vertices 100 / 117 us,
+// 20,001 148 / 131, 30,001 186 / 138; 2^19 entries, 8,001 190 / 216, 16,001 209
+// / 214, 30,001 272 / 254.
+constexpr int64_t kBinMinBatch = 20000;
 // ... and only grids whose binned levels split into this many slices (small
-// tables leave the reduce too few blocks).
-constexpr int kBinMinBins = 256;
+// tables leave the reduce too few blocks).  2^17 entries, 160 slices, chunked
+// scatter alone / binned: 40,001 vertices 204 / 159 us, 120,001 495 / 304,
+// 400,001 937 / 536, 1,000,001 2207 / 1753.
+constexpr int kBinMinBins = 128;
 // In a spatially ordered batch the hashed levels with D_l below this share
 // enough lines to stay with the chunked scatter.  Training step of the
 // 16-level production grid with the line at 100 / 140 / 180 / 250: 2^20
