@@ -25,7 +25,11 @@
  *
  * All request buffers are caller-owned DEVICE pointers in the layouts of
  * npm_query / npm_backward, and must stay valid until npm_wait returns for
- * the request.  Every call returns an npm_status and sets npm_last_error().
+ * the request.  A round's training batches use scratch of the server's own
+ * beside the budget (128 bytes per vertex, and 16 (2 + F) bytes per vertex and
+ * hashed level of the largest batch that is binned), which grows to the largest
+ * round and goes with the server; without room for it a round still runs, its
+ * grid scatter slower.  Every call returns an npm_status and sets npm_last_error().
  */
 #ifndef NPM_SERVE_H
 #define NPM_SERVE_H

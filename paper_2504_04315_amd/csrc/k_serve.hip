@@ -18,6 +18,7 @@ struct DevReq {
     const __half *grid16;
     const void *img;             // BF16 images of the session: forward then backward
     float *grad;                 // the session's gradient buffer (train)
+    float *dgt;                  // per-tile dG of the request (train), or null: scattered here
     const float *pos, *dir, *rad, *spdf;
     float *lobes, *pdf, *sdir, *spdf_out;
     double *loss;                // loss slot of the round buffer (train)
@@ -44,7 +45,10 @@ struct RoundHdr {
 static_assert(sizeof(RoundHdr) <= 64, "the round header sits in the first 64 bytes");
 
 constexpr int kQueryChunkTiles = 4;    // one tile per wave
-constexpr int kTrainChunkTiles = 16;   // four rounds of one tile per wave
+// Training chunks hold kTrainWaves tiles for each round of the block's waves, up
+// to four rounds (train_chunk_tiles).
+constexpr int kTrainWaves = 4;
+constexpr int kServeRows = 32;         // dG rows of a tile
 
 // Bytes of a training block's LDS exchange buffer (BF16, after the images).
 template <int IN_P, int HID_P, int NH>
@@ -109,22 +113,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 // Training batches of requests [r0, r1), the fused path's block-cooperative
-// scheme (fused_tiles.h): a chunk is kTrainChunkTiles tiles of one request,
-// run as rounds of one tile per wave; per layer the waves exchange deltas and
-// inputs in LDS and each wave accumulates its share of the weight-gradient
-// blocks over the round's 128 vertices.  The shares stay in registers while
-// the block's chunks belong to one request (its chunks are handed out in
-// order, so a block usually takes several in a row) and are added into that
-// session's gradient with FP32 atomics when the request changes and at the
-// end: per block and request, one add per weight.  Each tile's grid gradient
-// is scattered from the wave's LDS buffer, its coarse levels through a 32-bit
-// fixed-point window (no FP64 accumulator), the rest by FP32 atomics.
+// scheme (fused_tiles.h): a chunk is chunk_tiles tiles of one request, run as
+// rounds of one tile per wave; per layer the waves exchange deltas and inputs
+// in LDS and each wave accumulates its share of the weight-gradient blocks over
+// the round's 128 vertices.  The shares stay in registers while the block's
+// chunks belong to one request (its chunks are handed out in order, so a block
+// usually takes several in a row) and are added into that session's gradient
+// with FP32 atomics when the request changes and at the end: per block and
+// request, one add per weight.
+//
+// Each tile's dG goes to the request's buffer, for the chunked and binned
+// scatters of the per-session path, which sum in LDS (integer fixed point).
+// Scattered from here, 16 levels of 36,868 unordered vertices took 2.4 M line
+// requests of memory-side atomics from 73 blocks: 263 us, now 74 with two
+// rounds of tiles a chunk, so that every CU has a block, and 100 for the
+// scatters.  Only where the device has no room for the dG does a tile scatter
+// from the wave's LDS buffer, its coarse levels through a 32-bit fixed-point
+// window, the rest by FP32 atomics.
 template <int IN_P, int HID_P, int NH, int F>
 __global__ __launch_bounds__(256) void k_serve_train(RoundHdr *hdr, const DevReq *__restrict__ reqs,
                                                      int r0, int r1, int n_chunks, int which,
-                                                     int img_bytes_max)
+                                                     int chunk_tiles, int img_bytes_max)
 {
-    constexpr int WV = 4;
+    constexpr int WV = kTrainWaves;
     using Plan = BlockPlan<IN_P, HID_P, NH, WV>;
     constexpr int IN0 = Plan::IN0;
     constexpr int XS = Plan::xs(true);
@@ -179,9 +190,9 @@ __global__ __launch_bounds__(256) void k_serve_train(RoundHdr *hdr, const DevReq
         const char *fwd = smem;
         const char *bwd = smem + (size_t)q.fwd_elems * 2;
         const int64_t ntiles = (q.n + 31) / 32;
-        const int64_t c0 = (int64_t)(chunk - q.chunk_begin) * kTrainChunkTiles;
+        const int64_t c0 = (int64_t)(chunk - q.chunk_begin) * chunk_tiles;
         double lacc = 0.0;
-        for (int rr = 0; rr < kTrainChunkTiles / WV; ++rr) {
+        for (int rr = 0; rr < chunk_tiles / WV; ++rr) {
             // every wave runs every round of the chunk (the phases
             // synchronise); a wave past the batch takes a tile with no valid
             // vertex
@@ -221,8 +232,12 @@ __global__ __launch_bounds__(256) void k_serve_train(RoundHdr *hdr, const DevReq
             float dG[IN0 / 2];
             layer<true, HID_P, IN0>(im, dh, dG, lane);
             __syncthreads();
-            // ---- the tile's grid scatter from the wave's own buffer
-            if (t < ntiles) {
+            if (t < ntiles && q.dgt) {
+                float *dst = q.dgt + (size_t)t * kServeRows * 32 + (lane & 31);
+#pragma unroll
+                for (int i = 0; i < IN0 / 2; ++i) dst[nf(h, i) * 32] = dG[i];
+            } else if (t < ntiles) {
+                // the tile's grid scatter from the wave's own buffer
                 float lo[3], hi[3];
                 if constexpr (WIN_PTS > 0) tile_bbox(in.px, in.py, in.pz, lo, hi);
                 wave_lds_fence();
@@ -281,6 +296,46 @@ void round_buffers_free(RoundBuffers *b)
     b->host = b->dev = nullptr;
 }
 
+hipError_t serve_lanes_init(ServeLanes *l)
+{
+    hipError_t e = hipStreamCreateWithFlags(&l->side, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&l->fork, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&l->join, hipEventDisableTiming);
+    return e;
+}
+
+void serve_lanes_free(ServeLanes *l)
+{
+    if (l->side) (void)hipStreamDestroy(l->side);
+    if (l->fork) (void)hipEventDestroy(l->fork);
+    if (l->join) (void)hipEventDestroy(l->join);
+    for (ServeBuf *b : {&l->dgt, &l->cnt, &l->items})
+        if (b->p) (void)hipFree(b->p);
+    *l = ServeLanes{};
+}
+
+// Grows b to `words` 32-bit words.  The rounds before this one may still use
+// it: their stream is drained first (and it has waited for the side stream).
+// False, with b empty, where the device has no room.  The scheduler's thread
+// allocates whatever another thread's streams are capturing.
+static bool grow(ServeBuf *b, size_t words, hipStream_t s)
+{
+    if (words <= b->words) return true;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
+    bool ok = hipStreamSynchronize(s) == hipSuccess;
+    if (ok) {
+        if (b->p) (void)hipFree(b->p);
+        b->p = nullptr;
+        b->words = 0;
+        ok = hipMalloc((void **)&b->p, words * 4) == hipSuccess;
+        if (ok) b->words = words;
+        else (void)hipGetLastError();
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return ok;
+}
+
 static int shape_key(const Net &net)
 {
     const MlpDesc &m = net.mlp;
@@ -300,7 +355,8 @@ bool serve_supports(const npm_config *cfg)
 
 template <int IN_P, int HID_P, int NH, int F>
 static hipError_t launch_group(RoundHdr *hdr, const DevReq *reqs, int r0, int r1, int chunks,
-                               int which, bool train, int img_bytes_max, hipStream_t s)
+                               int which, bool train, int chunk_tiles, bool tile_scatter,
+                               int img_bytes_max, hipStream_t s)
 {
     if (chunks <= 0) return hipSuccess;
     const int blocks = std::max(1, std::min(chunks, 1024));
@@ -313,34 +369,76 @@ static hipError_t launch_group(RoundHdr *hdr, const DevReq *reqs, int r0, int r1
         hipLaunchKernelGGL(k, dim3(blocks), dim3(256), lds, s, hdr, reqs, r0, r1, chunks, which);
     } else {
         auto k = k_serve_train<IN_P, HID_P, NH, F>;
-        // images, the exchange buffer, four waves' scatter buffers
+        // images, the exchange buffer, and where a request is scattered tile by
+        // tile the four waves' buffers for that
         const int lds = (img_bytes_max + 15) / 16 * 16 + (int)serve_xch_bytes<IN_P, HID_P, NH>() +
-                        4 * HID_P * kStride * (int)sizeof(float);
+                        (tile_scatter ? 4 * HID_P * kStride * (int)sizeof(float) : 0);
         const hipError_t e = hipFuncSetAttribute((const void *)k,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k, dim3(std::min(blocks, 256)), dim3(256), lds, s, hdr, reqs, r0, r1,
-                           chunks, which, img_bytes_max);
+                           chunks, which, chunk_tiles, img_bytes_max);
     }
     return hipGetLastError();
 }
 
 static hipError_t launch_shape(int key, RoundHdr *hdr, const DevReq *reqs, int r0, int r1,
-                               int chunks, int which, bool train, int img_bytes_max, hipStream_t s)
+                               int chunks, int which, bool train, int chunk_tiles,
+                               bool tile_scatter, int img_bytes_max, hipStream_t s)
 {
     switch (key) {
-    case 2113: return launch_group<32, 64, 3, 2>(hdr, reqs, r0, r1, chunks, which, train, img_bytes_max, s);
-    case 2112: return launch_group<32, 64, 2, 2>(hdr, reqs, r0, r1, chunks, which, train, img_bytes_max, s);
-    case 4012: return launch_group<16, 64, 2, 4>(hdr, reqs, r0, r1, chunks, which, train, img_bytes_max, s);
-    case 2002: return launch_group<16, 32, 2, 2>(hdr, reqs, r0, r1, chunks, which, train, img_bytes_max, s);
+    case 2113: return launch_group<32, 64, 3, 2>(hdr, reqs, r0, r1, chunks, which, train, chunk_tiles, tile_scatter, img_bytes_max, s);
+    case 2112: return launch_group<32, 64, 2, 2>(hdr, reqs, r0, r1, chunks, which, train, chunk_tiles, tile_scatter, img_bytes_max, s);
+    case 4012: return launch_group<16, 64, 2, 4>(hdr, reqs, r0, r1, chunks, which, train, chunk_tiles, tile_scatter, img_bytes_max, s);
+    case 2002: return launch_group<16, 32, 2, 2>(hdr, reqs, r0, r1, chunks, which, train, chunk_tiles, tile_scatter, img_bytes_max, s);
     default: return hipErrorNotSupported;
     }
 }
 
+// Tiles of a training chunk: up to four rounds of a tile per wave, as many as
+// leave every CU a block.
+static int train_chunk_tiles(int64_t tiles)
+{
+    const int64_t rounds = (tiles + 256 * kTrainWaves - 1) / (256 * kTrainWaves);
+    return kTrainWaves * (int)std::max<int64_t>(1, std::min<int64_t>(4, rounds));
+}
+
+// The binned levels of a training request (in its own order), or false.
+static bool request_bins(const ServeRequest &q, BinDesc *b)
+{
+    const int mode = q.ctx->net.cfg.scatter_mode;
+    return mode != NPM_SCATTER_ATOMIC && (mode == NPM_SCATTER_BINNED || q.n >= kBinMinBatch) &&
+           bin_plan(q.ctx, q.n, false, b) && (mode == NPM_SCATTER_BINNED || b->nbins >= kBinMinBins);
+}
+
+// The grid scatter of one request's dG (in the request's order: its bins hold
+// every hashed level).
+static hipError_t scatter_request(const ServeRequest &q, ServeLanes *l, const float *dgt,
+                                  hipStream_t s)
+{
+    const GridDesc &g = q.ctx->net.grid;
+    BinDesc b;
+    const bool binned = request_bins(q, &b) && l->cnt.words >= bin_count_words(b) &&
+                        l->items.words >= bin_item_words(b, g.feat);
+    uint32_t left = g.n_levels >= 32 ? ~0u : (1u << g.n_levels) - 1u;
+    if (binned)
+        for (int j = 0; j < b.nb; ++j) left &= ~(1u << b.lv[j]);
+    hipError_t e = chunk_scatter(q.ctx->net, q.n, q.pos, nullptr, nullptr, 8, dgt, kServeRows,
+                                 q.ctx->grads, left, s);
+    if (e == hipSuccess && binned)
+        e = binned_scatter(q.ctx, b, q.n, q.pos, nullptr, nullptr, 8, dgt, kServeRows,
+                           q.ctx->grads, l->cnt.p, l->items.p, false, s);
+    return e;
+}
+
 // Round buffer: [header][DevReq x n][loss x n][stats pointer x n].  Requests
 // are ordered by (shape, kind) so that each launch covers a contiguous range.
-hipError_t serve_launch_round(RoundBuffers *b, const std::vector<ServeRequest> &in,
-                              hipStream_t s)
+// With both kinds in a round the queries run on the side stream beside the
+// training kernels (both only read the weights); the Adam steps follow both.
+// Eight queries of 2^10 .. 2^17 vertices and two training batches, one stream /
+// two: 587 / 545 us a round, submission and completion included.
+hipError_t serve_launch_round(RoundBuffers *b, ServeLanes *lanes,
+                              const std::vector<ServeRequest> &in, hipStream_t s)
 {
     const RoundLayout L = round_layout();
     const int nreq = (int)in.size();
@@ -363,15 +461,34 @@ hipError_t serve_launch_round(RoundBuffers *b, const std::vector<ServeRequest> &
     double **hstats = (double **)(host + L.stats);
     DevReq *dr = (DevReq *)(dev + L.reqs);
     double *dloss = (double *)(dev + L.loss);
-    struct Group { int key, kind, r0, r1, chunks, img; };
+    struct Group { int key, kind, r0, r1, chunks, img, tiles; };
     std::vector<Group> groups;
+    // dG of the round's training batches, one after the other, and the bins of
+    // one batch at a time
+    size_t dgt_words = 0, cnt_words = 0, item_words = 0;
+    int64_t train_tiles = 0;
+    for (const ServeRequest &q : in) {
+        if (q.kind == 0) continue;
+        const int64_t tiles = (q.n + 31) / 32;
+        train_tiles += tiles;
+        dgt_words += (size_t)tiles * kServeRows * 32;
+        BinDesc bd;
+        if (request_bins(q, &bd)) {
+            cnt_words = std::max(cnt_words, bin_count_words(bd));
+            item_words = std::max(item_words, bin_item_words(bd, q.ctx->net.grid.feat));
+        }
+    }
+    const int per_train = train_chunk_tiles(train_tiles);
+    const bool dgt = grow(&lanes->dgt, dgt_words, s);
+    if (dgt && grow(&lanes->cnt, cnt_words, s)) (void)grow(&lanes->items, item_words, s);
+    size_t dgt_at = 0;
     for (int j = 0; j < nreq; ++j) {
         const ServeRequest &q = in[order[j]];
         npm_ctx *ctx = q.ctx;
         const Net &net = ctx->net;
         const int key = shape_key(net);
         if (groups.empty() || groups.back().key != key || groups.back().kind != q.kind)
-            groups.push_back({key, q.kind, j, j, 0, 0});
+            groups.push_back({key, q.kind, j, j, 0, 0, q.kind == 0 ? kQueryChunkTiles : per_train});
         Group &g = groups.back();
         DevReq &d = hr[j];
         std::memset(&d, 0, sizeof(d));
@@ -394,9 +511,12 @@ hipError_t serve_launch_round(RoundBuffers *b, const std::vector<ServeRequest> &
         d.width = net.mlp.width;
         d.invN = q.n > 0 ? 1.0f / (float)q.n : 0.0f;
         const int64_t tiles = (q.n + 31) / 32;
-        const int per = q.kind == 0 ? kQueryChunkTiles : kTrainChunkTiles;
+        if (q.kind == 1 && dgt) {
+            d.dgt = (float *)lanes->dgt.p + dgt_at;
+            dgt_at += (size_t)tiles * kServeRows * 32;
+        }
         d.chunk_begin = g.chunks;
-        g.chunks += (int)((tiles + per - 1) / per);
+        g.chunks += (int)((tiles + g.tiles - 1) / g.tiles);
         g.r1 = j + 1;
         const int img = (int)((q.kind == 0 ? net.mlp.fwd_elems : net.mlp.fwd_elems + net.mlp.bwd_elems) * 2);
         g.img = std::max(g.img, img);
@@ -408,24 +528,50 @@ hipError_t serve_launch_round(RoundBuffers *b, const std::vector<ServeRequest> &
     hipError_t e = hipMemcpyAsync(dev, host, L.total, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return e;
     RoundHdr *dh = (RoundHdr *)dev;
-    for (int gi = 0; gi < (int)groups.size(); ++gi) {
-        const Group &g = groups[gi];
-        e = launch_shape(g.key, dh, dr, g.r0, g.r1, g.chunks, gi, g.kind == 1, g.img, s);
+    bool trains = false, both = false;
+    for (const Group &g : groups) trains |= g.kind == 1;
+    for (const Group &g : groups) both |= trains && g.kind == 0;
+    hipStream_t sq = s;                      // the queries' stream
+    if (both) {
+        sq = lanes->side;
+        e = hipEventRecord(lanes->fork, s);
+        if (e == hipSuccess) e = hipStreamWaitEvent(sq, lanes->fork, 0);
         if (e != hipSuccess) return e;
-        if (g.kind == 1) {
-            hipLaunchKernelGGL(k_serve_finish, dim3((g.r1 - g.r0 + 63) / 64), dim3(64), 0, s, dr,
-                               (const double *const *)(dev + L.stats), g.r0, g.r1);
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            for (int j = g.r0; j < g.r1; ++j) {
-                const ServeRequest &q = in[order[j]];
-                q.ctx->step += 1;
-                e = launch_adam(q.ctx, q.ctx->grads, q.stats ? q.stats + 1 : nullptr, s);
-                if (e != hipSuccess) return e;
-            }
+    }
+    // the training kernels first: a block of theirs needs a CU's registers
+    for (int kind = 1; kind >= 0; --kind)
+        for (int gi = 0; gi < (int)groups.size() && e == hipSuccess; ++gi) {
+            const Group &g = groups[gi];
+            if (g.kind != kind) continue;
+            e = launch_shape(g.key, dh, dr, g.r0, g.r1, g.chunks, gi, kind == 1, g.tiles, !dgt,
+                             g.img, kind == 0 ? sq : s);
+        }
+    for (int gi = 0; gi < (int)groups.size() && e == hipSuccess; ++gi) {
+        const Group &g = groups[gi];
+        if (g.kind != 1) continue;
+        hipLaunchKernelGGL(k_serve_finish, dim3((g.r1 - g.r0 + 63) / 64), dim3(64), 0, s, dr,
+                           (const double *const *)(dev + L.stats), g.r0, g.r1);
+        e = hipGetLastError();
+        for (int j = g.r0; j < g.r1 && dgt && e == hipSuccess; ++j)
+            e = scatter_request(in[order[j]], lanes, hr[j].dgt, s);
+    }
+    // joined whatever failed: what follows on s, and the round's end, come
+    // after the queries too
+    if (both) {
+        hipError_t ej = hipEventRecord(lanes->join, sq);
+        if (ej == hipSuccess) ej = hipStreamWaitEvent(s, lanes->join, 0);
+        if (ej != hipSuccess) (void)hipStreamSynchronize(sq);
+        if (e == hipSuccess) e = ej;
+    }
+    for (int gi = 0; gi < (int)groups.size() && e == hipSuccess; ++gi) {
+        const Group &g = groups[gi];
+        for (int j = g.r0; g.kind == 1 && j < g.r1 && e == hipSuccess; ++j) {
+            const ServeRequest &q = in[order[j]];
+            q.ctx->step += 1;
+            e = launch_adam(q.ctx, q.ctx->grads, q.stats ? q.stats + 1 : nullptr, s);
         }
     }
-    return hipSuccess;
+    return e;
 }
 
 }  // namespace npm

@@ -86,6 +86,7 @@ struct npm_server {
     std::condition_variable cv_inflight;
     bool slot_busy[kSlots] = {false, false, false, false};
     RoundBuffers bufs[kSlots];
+    ServeLanes lanes;             // the scheduler thread's
     uint64_t next_id = 1;
     int64_t next_round = 0;
     int64_t bytes_in_use = 0;
@@ -145,6 +146,7 @@ hipError_t execute_plain(const std::vector<ServeRequest> &work, hipStream_t stre
 
 void scheduler(npm_server *s)
 {
+    (void)hipSetDevice(s->device);    // the lanes' scratch belongs to the sessions' device
     std::unique_lock<std::mutex> lk(s->mu);
     for (;;) {
         s->cv_sched.wait(lk, [&] { return s->stop || (!s->pending.empty() && !s->held); });
@@ -190,7 +192,8 @@ void scheduler(npm_server *s)
         }
         lk.unlock();
         const hipError_t e = plain ? execute_plain(work, s->stream)
-                                   : serve_launch_round(&s->bufs[slot], work, s->stream);
+                                   : serve_launch_round(&s->bufs[slot], &s->lanes, work,
+                                                        s->stream);
         // The event follows whatever part of the round did launch (also when
         // a later launch failed): the completion thread releases the round's
         // descriptor buffer only after the device has passed it.  Without an
@@ -266,7 +269,9 @@ npm_status npm_server_create(const npm_server_config *cfg, npm_server **out)
     hipError_t e = hipGetDevice(&s->device);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking);
     for (int i = 0; i < kSlots && e == hipSuccess; ++i) e = round_buffers_init(&s->bufs[i]);
+    if (e == hipSuccess) e = serve_lanes_init(&s->lanes);
     if (e != hipSuccess) {
+        serve_lanes_free(&s->lanes);
         for (int i = 0; i < kSlots; ++i) round_buffers_free(&s->bufs[i]);
         if (s->stream) (void)hipStreamDestroy(s->stream);
         delete s;
@@ -316,6 +321,7 @@ npm_status npm_server_destroy(npm_server *s)
     (void)hipStreamSynchronize(s->stream);
     for (auto &se : s->sessions)
         if (se.alive) npm_destroy(se.ctx);
+    serve_lanes_free(&s->lanes);
     for (int i = 0; i < kSlots; ++i) round_buffers_free(&s->bufs[i]);
     (void)hipStreamDestroy(s->stream);
     delete s;

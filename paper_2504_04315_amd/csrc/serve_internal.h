@@ -30,14 +30,32 @@ struct RoundBuffers {
     size_t bytes = 0;
 };
 
+// The server's second stream (default priority) for rounds of both kinds, and
+// the training scratch of a round: the per-tile dG of its batches and the bins
+// of one of them.  The rounds of a server run one after the other on its
+// stream, so one set serves them all; it grows to the largest round and goes
+// with the server.
+struct ServeBuf {
+    uint32_t *p = nullptr;
+    size_t words = 0;
+};
+struct ServeLanes {
+    hipStream_t side = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
+    ServeBuf dgt, cnt, items;
+};
+
+hipError_t serve_lanes_init(ServeLanes *l);
+void serve_lanes_free(ServeLanes *l);
 hipError_t round_buffers_init(RoundBuffers *b);
 void round_buffers_free(RoundBuffers *b);
 // Whether the persistent kernels are instantiated for this network shape.
 bool serve_supports(const npm_config *cfg);
-// Enqueues one round on `s`: the persistent query kernel over every query of
-// the round, the persistent backward kernel over every training batch, and
-// the Adam step of each session that trained.
-hipError_t serve_launch_round(RoundBuffers *b, const std::vector<ServeRequest> &reqs,
-                              hipStream_t s);
+// Enqueues one round on `s` (and beside it on the lanes' side stream, which `s`
+// waits for): the persistent query kernel over every query of the round, the
+// persistent backward kernel over every training batch, each batch's grid
+// scatter, and the Adam step of each session that trained.
+hipError_t serve_launch_round(RoundBuffers *b, ServeLanes *lanes,
+                              const std::vector<ServeRequest> &reqs, hipStream_t s);
 
 }  // namespace npm
