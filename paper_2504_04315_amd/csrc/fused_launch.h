@@ -33,6 +33,7 @@ struct FusedArgs {
     const float *bsdf;       // BSDF densities [n] of the selection term (backward), or null
     double *partials_sel;    // per-block FP64 partials of the selection loss
     float *sel;              // selection probability [n] (query), or null
+    int tile_v, halves;      // vertices per block and blocks per tile (k_query_small)
     const void *feat;        // level-major grid features of the batch (k_encode.hip)
     const __bf16 *img_t;     // packed BF16 image of W^T (the backward image), and the two
     const __bf16 *img_split; // further planes of its three-way split (FP32 training)

@@ -171,11 +171,17 @@ __global__ __launch_bounds__(64) void k_query_small(FusedArgs a)
     __shared__ __attribute__((aligned(16))) float s_wsel[SEL ? HID_P : 4];
     constexpr int ING = PG > 0 ? ProductShape<PG>::GF : IN_P;
     constexpr size_t ESZ = BF ? 2 : 4;
-    const QueryIO io{a.n, a.pos, a.dir, a.lobes, a.pdf, a.sdir, a.spdf_out, a.seed, a.sid,
-                     nullptr, nullptr, nullptr, a.aux, a.rec_stride, a.sel, s_wsel};
-    const int lane = threadIdx.x & 63, h = lane >> 5;
-    const int64_t n = a.n, slot = blockIdx.x * (int64_t)32 + (lane & 31);
+    // of a tile's two blocks one answers the lobes and the pdf, one the samples
+    const int part = a.halves == 2 ? (int)(blockIdx.x & 1) : -1;
+    const QueryIO io{a.n, a.pos, a.dir, part == 1 ? nullptr : a.lobes, part == 1 ? nullptr : a.pdf,
+                     part == 0 ? nullptr : a.sdir, part == 0 ? nullptr : a.spdf_out, a.seed, a.sid,
+                     nullptr, nullptr, nullptr, a.aux, a.rec_stride, part == 1 ? nullptr : a.sel,
+                     s_wsel};
+    const int lane = threadIdx.x & 63, h = lane >> 5, j = lane & 31;
+    const int64_t n = a.n;
+    const int64_t slot = (blockIdx.x / a.halves) * (int64_t)a.tile_v + min(j, a.tile_v - 1);
     const int64_t v = slot < n ? slot : n - 1;
+    const bool valid = j < a.tile_v && slot < n;
     const int gf = a.g.n_levels * F;
     FeatWords<ING, BF> fw;
     TileGather<ING, F, BF> tg;
@@ -195,7 +201,7 @@ __global__ __launch_bounds__(64) void k_query_small(FusedArgs a)
     LayerRegs<BF, HID_P, 32> lo;
     const char *img = reinterpret_cast<const char *>(a.img);
     float wx = 0.0f, wy = 0.0f, wz = 0.0f;
-    if (a.pdf) { wx = a.dir[v]; wy = a.dir[n + v]; wz = a.dir[2 * n + v]; }
+    if (io.pdf) { wx = a.dir[v]; wy = a.dir[n + v]; wz = a.dir[2 * n + v]; }
     l0.load(img, lane);
 #pragma unroll
     for (int i = 0; i < NH - 1; ++i) lh[i].load(img + (size_t)(IN_P + i * HID_P) * HID_P * ESZ, lane);
@@ -239,7 +245,7 @@ __global__ __launch_bounds__(64) void k_query_small(FusedArgs a)
     }
     if constexpr (SEL) cp = select_logit<HID_P>(s_wsel, p, h);
     lo.apply(p, o);
-    query_head<SEL>(io, v, slot < n, nullptr, lane, o, cp, wx, wy, wz);
+    query_head<SEL>(io, v, valid, nullptr, lane, o, cp, wx, wy, wz);
 }
 
 // Moves the staged outputs of a spatially ordered query to the caller's SoA
@@ -307,7 +313,15 @@ static hipError_t run_query_feat(npm_ctx *ctx, FusedArgs a, hipStream_t s)
 template <int IN_P, int HID_P, int NH, int F, bool BF, int PG = 0, bool SEL = false>
 static hipError_t run_query_small(npm_ctx *ctx, FusedArgs a, hipStream_t s)
 {
-    const dim3 grid((unsigned)((a.n + 31) / 32));
+    // Up to a block per CU the tiles are split further: half-filled ones, whose
+    // gathers are half as many requests of a CU, and the answers of a tile that
+    // asks for both kinds shared by two blocks, which repeat the network.  16
+    // levels, 2^19 entries, FP32: 1,000 vertices 18.9 -> 17.6 us, 2,048 19.2 ->
+    // 19.0, but 4,096 20.1 -> 22.5.
+    const bool tiny = a.n <= kQueryTiny, both = (a.lobes || a.pdf || a.sel) && (a.sdir || a.spdf_out);
+    a.tile_v = tiny ? 16 : 32;
+    a.halves = tiny && both ? 2 : 1;
+    const dim3 grid((unsigned)((a.n + a.tile_v - 1) / a.tile_v * a.halves));
     if (a.feat)
         hipLaunchKernelGGL((k_query_small<IN_P, HID_P, NH, F, BF, PG, SEL, false>), grid, dim3(64), 0,
                            s, a);

@@ -299,6 +299,8 @@ bool fused_shape_supported(const Net &net);
 // one weight image in LDS.  On the 8-level dense grid, FP32, 4,096 vertices
 // 20.3 -> 16.3 us, 32,768 23.0 -> 20.9 us, and 65,536 would be 41 against 34 us.
 constexpr int64_t kQuerySmall = 1 << 15;
+// Of those, the ones of at most this many are split over more blocks (k_query.hip).
+constexpr int64_t kQueryTiny = 2048;
 // Queries of more vertices than this on a grid with hashed levels encode the
 // batch level by level first (k_encode.hip): the second launch costs 3 us,
 // and up to here gathering every corner of a tile at once is no slower.  16

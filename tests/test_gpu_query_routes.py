@@ -43,7 +43,7 @@ def test_every_route_gives_the_same_bits(torch, name, prec):
     n_max = 65537
     full = W.make_batch("surface", n_max, seed=9)
     full_aux = W.make_aux(full, 9) if net.sh_degree else None
-    for n in (1, 31, 33, 16384, 16385, 24577, 32768, 32769, n_max):
+    for n in (1, 31, 33, 2047, 2049, 16384, 16385, 24577, 32768, 32769, n_max):
         pos, d = dev(full.pos[:, :n]), dev(full.dir[:, :n])
         kw = dict(seed=3, stream_id=4)
         if net.sh_degree:
@@ -52,5 +52,16 @@ def test_every_route_gives_the_same_bits(torch, name, prec):
         torch.cuda.synchronize()
         for k, v in qa.items():
             assert torch.equal(v, qb[k]), (n, k, (v - qb[k]).abs().max().item())
+    # a small batch's blocks share the answers of a tile that asks for both kinds
+    pos, d = dev(full.pos[:, :999]), dev(full.dir[:, :999])
+    kw = dict(seed=3, stream_id=4)
+    if net.sh_degree:
+        kw["aux"] = dev(full_aux[:, :999])
+    call = a.query_select if net.select else a.query
+    every = call(pos, d, **kw)
+    for part in (dict(sample=False), dict(lobes=False, pdf=False), dict(lobes=False, sample=False),
+                 dict(pdf=False)):
+        for k, v in call(pos, d, **part, **kw).items():
+            assert v is None or torch.equal(v, every[k]), (part, k)
     a.close()
     b.close()
