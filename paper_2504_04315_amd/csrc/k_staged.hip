@@ -110,11 +110,11 @@ __device__ __forceinline__ void store_tile(float *__restrict__ dst, int rows, in
 
 // ============================================================= MLP forward
 // Wave tiles of 32 vertices in a grid-stride loop; all layer images in LDS.
-// acts (optional) receives every hidden layer's output [n_hidden][width][n].
+// With ACTS acts receives every hidden layer's output [n_hidden][width][n].
 // wsel (or null): the selection row of the last layer, width weights; its
 // output goes to raw row kOut.
-template <int IN_P, int HID_P, int NH>
-__global__ __launch_bounds__(256) void k_mlp_fwd(int64_t n, int n_in, int width,
+template <int IN_P, int HID_P, int NH, bool ACTS>
+__global__ __launch_bounds__(256, !ACTS && IN_P <= 32 ? 3 : 1) void k_mlp_fwd(int64_t n, int n_in, int width,
                                                  const float *__restrict__ img, int img_elems,
                                                  const float *__restrict__ G,
                                                  float *__restrict__ acts, float *__restrict__ raw,
@@ -128,20 +128,41 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(int64_t n, int n_in, int width,
     const int64_t wave = blockIdx.x * (int64_t)(blockDim.x / 64) + (threadIdx.x >> 6);
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / 64);
     constexpr int L0 = 0, L1 = HID_P * IN_P;           // image offsets of layer 0 and 1
+    // The next tile's inputs are in flight during this one; the loads are not
+    // masked (a masked load waits behind its branch), rows past the last read row
+    // 0 and count as zero.  The form that keeps the activations has kernels of
+    // its own: their addresses took the other one to 368 registers and a wave per
+    // SIMD (now three).  100,003 vertices, 32 -> 64 x 3 -> 32: 52 -> 38 us, 16 of
+    // them FP32 matrix time.
+    float xn[IN_P / 2];
+    auto load_next = [&](int64_t t) {
+        const int64_t v = t * 32 + (lane & 31), vs = v < n ? v : n - 1;
+#pragma unroll
+        for (int i = 0; i < IN_P / 2; ++i) {
+            const int f = nf(h, i);
+            xn[i] = G[(int64_t)(f < n_in ? f : 0) * n + vs];
+        }
+    };
+    if (wave < ntiles) load_next(wave);
     for (int64_t t = wave; t < ntiles; t += nwaves) {
         const int64_t v = t * 32 + (lane & 31);
         float x[IN_P / 2], a[HID_P / 2], b[HID_P / 2];
-        load_tile<IN_P / 2>(G, n_in, n, v, h, x);
+#pragma unroll
+        for (int i = 0; i < IN_P / 2; ++i) x[i] = v < n && nf(h, i) < n_in ? xn[i] : 0.0f;
+        if (t + nwaves < ntiles) load_next(t + nwaves);
+        // the arrays' strides are products of n: formed anew for each tile
+        // rather than kept
+        asm volatile("" : "+s"(n));
         mfma_layer_f32<IN_P, HID_P>(lds + L0, x, a, lane);
 #pragma unroll
         for (int i = 0; i < HID_P / 2; ++i) a[i] = fmaxf(a[i], 0.0f);
-        if (acts) store_tile<HID_P / 2>(acts, width, n, v, h, a);
+        if constexpr (ACTS) store_tile<HID_P / 2>(acts, width, n, v, h, a);
 #pragma unroll
         for (int layer = 1; layer < NH; ++layer) {
             mfma_layer_f32<HID_P, HID_P>(lds + L1 + (layer - 1) * HID_P * HID_P, a, b, lane);
 #pragma unroll
             for (int i = 0; i < HID_P / 2; ++i) a[i] = fmaxf(b[i], 0.0f);
-            if (acts) store_tile<HID_P / 2>(acts + (int64_t)layer * width * n, width, n, v, h, a);
+            if constexpr (ACTS) store_tile<HID_P / 2>(acts + (int64_t)layer * width * n, width, n, v, h, a);
         }
         float o[16];
         mfma_layer_f32<HID_P, 32>(lds + L1 + (NH - 1) * HID_P * HID_P, a, o, lane);
@@ -538,11 +559,12 @@ struct MlpFwd {
     {
         const MlpDesc &m = ctx->net.mlp;
         const int elems = (int)m.fwd_elems;
-        const hipError_t e = hipFuncSetAttribute((const void *)k_mlp_fwd<IN_P, HID_P, NH>,
+        auto k = acts ? k_mlp_fwd<IN_P, HID_P, NH, true> : k_mlp_fwd<IN_P, HID_P, NH, false>;
+        const hipError_t e = hipFuncSetAttribute((const void *)k,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  elems * sizeof(float));
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_mlp_fwd<IN_P, HID_P, NH>), dim3(blocks), dim3(256),
+        hipLaunchKernelGGL(k, dim3(blocks), dim3(256),
                            elems * sizeof(float), s, n, m.n_in, m.width, img, elems, G,
                            acts, raw, wsel);
         return hipGetLastError();
