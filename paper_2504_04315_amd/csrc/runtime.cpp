@@ -651,6 +651,14 @@ static hipError_t ensure_sort(npm_ctx *ctx, int64_t n)
     return hipSuccess;
 }
 
+// The per-tile dG of a training batch and, behind it, the batch's features
+// where the tile kernel reads them (train_feat): one allocation, which the
+// first step of a size waits for.
+static float *train_features(npm_ctx *ctx)
+{
+    return ctx->s_dgt + ctx->dgt_tiles * (int64_t)std::max(ctx->net.mlp.in_p, 32) * 32;
+}
+
 static hipError_t ensure_dgt(npm_ctx *ctx, int64_t n)
 {
     const int64_t tiles = (n + 31) / 32;
@@ -661,7 +669,8 @@ static hipError_t ensure_dgt(npm_ctx *ctx, int64_t n)
     ctx->s_dgt = nullptr;
     ctx->dgt_tiles = 0;
     const int64_t rows = std::max(ctx->net.mlp.in_p, 32);
-    e = hipMalloc((void **)&ctx->s_dgt, (size_t)tiles * rows * 32 * sizeof(float));
+    const size_t feat = train_feat(ctx) ? feat_words(ctx->net, tiles * 32) : 0;
+    e = hipMalloc((void **)&ctx->s_dgt, ((size_t)tiles * rows * 32 + feat) * sizeof(float));
     if (e != hipSuccess) return e;
     ctx->dgt_tiles = tiles;
     return hipSuccess;
@@ -686,11 +695,7 @@ static npm_status backward_impl(npm_ctx *ctx, int64_t n, const float *pos, const
                                   binned ? bin_clear_words(bins) : 0), "spatial order");
             perm = ctx->s_perm;
         }
-        void *feat = nullptr;
-        if (grad && train_feat(ctx)) {
-            NPM_HIP(ensure_feat(ctx, n), "feature scratch allocation");
-            feat = ctx->s_feat;
-        }
+        void *feat = grad && train_feat(ctx) ? train_features(ctx) : nullptr;
         NPM_HIP(fused_backward(ctx, n, pos, aux, dir, rad, spdf, grad, loss_out, perm,
                                perm ? ctx->s_rec : nullptr, grad ? ctx->s_dgt : nullptr,
                                binned ? &bins : nullptr, s, bsdf, feat),
