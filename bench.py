@@ -70,7 +70,7 @@ WORK = {
 # ordered batch: levels 6-15 (D >= 100), 2^19 entries x F = 2 each, in slices
 # of 8,192 entries: 640 bins; chunks of 1,024 vertices; one 16-byte item (the
 # key, the x fraction, 2 FP32 values) per pair of x-neighbour corners and
-# level.  Levels 0-5 keep the windowed scatter.
+# level.  Levels 0-5 keep the chunked scatter.
 L_BINNED, L_WINDOW, T_HASH = 10, 6, 1 << 19
 BIN_ITEM_B = 16
 BIN_ITEMS_B = L_BINNED * 4 * BIN_ITEM_B           # 640 B per vertex
@@ -84,7 +84,7 @@ BIN_WORK = {
     # (its per-vertex share at 2^20 vertices is added in main)
     "bin_reduce": dict(bytes=BIN_ITEMS_B, flops=0),
 }
-# with those levels binned the windowed scatter covers levels 0-5
+# with those levels binned the chunked scatter covers levels 0-5
 FUSED_SCATTER_DENSE_B = 12 + 4 + 32 * 4 + 2 * 8 * 2 * 4 * L_WINDOW
 ADAM_BYTES_PER_PARAM = 32      # read p, g, m, v; write p, m, v, g
 # FP32 global atomics with random addresses, one 64-byte line per request,
@@ -498,6 +498,15 @@ def main():
     measured = load_profile("counters", f"cfg2_{args.precision}_{args.mode}", sha)
     np_params = model.n_params
     work = dict(WORK)
+    # encoded level by level first: the gathers are the encode's, the other
+    # kernels read its features (FP32, or BF16 in the precision form)
+    feat_b = 32 * (2 if args.precision == "bf16" else 4)
+    if "query_encode" in kt:
+        work["query_encode"] = dict(bytes=12 + GATHER_B + feat_b, flops=0)
+        work["fused_query"] = dict(bytes=24 + feat_b + 148, flops=MLP_F)
+    if "train_encode" in kt:
+        work["train_encode"] = dict(bytes=16 + GATHER_B + feat_b, flops=0)
+        work["fused_backward"] = dict(bytes=32 + feat_b + 32 * 4, flops=3 * MLP_F)
     if "bin_reduce" in kt:
         work.update(BIN_WORK)
         work["bin_reduce"] = dict(bytes=BIN_ITEMS_B + 2 * L_BINNED * T_HASH * 2 * 4 / n, flops=0)

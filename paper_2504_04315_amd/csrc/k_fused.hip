@@ -1,19 +1,18 @@
-// Fused execution of the NPM hot path.  A wave owns a tile of 32 vertices and
-// keeps it on chip from the grid lookup to the outputs:
-//
-//   query:     encode (Sec. 5.1) -> MLP on MFMA (Sec. 5.3) -> Table 1 mappings
-//              -> mixture pdf at dir -> lobe selection and vMF sample (Jakob
-//              2012) -> pdf at the sample.
-//   backward:  encode -> MLP forward (activations in registers) -> KL-gradient
-//              head (Sec. 4.2, eq. mcgradients) -> delta chain -> weight
-//              gradients (MFMA with the tile's vertices as the reduction
-//              dimension, accumulated per wave) -> the tile's dG stored;
-//              then the aggregated grid scatter (FP32 atomics) in a kernel of
-//              its own.
-// Batches of 2^15 vertices or more are visited in a spatial order (k_sort.hip)
-// with their inputs read from one record per slot; a query's outputs are
-// staged per slot and un-permuted.  NPM-product kernels (PG > 0) also take
-// the outgoing direction, normal and roughness (Sec. 4.3).
+// Fused training of the NPM hot path: the launches of a gradient (features,
+// tile kernel, scatters, weight-gradient sum), and the training kernel that
+// gathers the grid's corners itself.  A wave owns a tile of 32 vertices and keeps
+// it on chip: encode (Sec. 5.1) -> MLP forward (Sec. 5.3, activations in
+// registers) -> KL-gradient head (Sec. 4.2, eq. mcgradients) -> delta chain ->
+// weight gradients (MFMA with the tile's vertices as the reduction dimension)
+// -> the tile's dG stored; then the grid scatter in kernels of its own.  The
+// gathering kernel serves the allocation-free call (its fixed scratch holds no
+// features), the FP32 form of the wide NPM-product input and the precision
+// form's loss alone; every other gradient runs k_train_tile (k_train.hip) on
+// features encoded level by level.
+// Batches of kSortMinBatch vertices or more are visited in a spatial order
+// (k_sort.hip) with their inputs read from one record per slot.  NPM-product
+// kernels (PG > 0) also take the outgoing direction, normal and roughness
+// (Sec. 4.3).
 //
 // Tile layout (device_math.h): lane l holds vertex l % 32; of a feature vector
 // the half-wave h = l / 32 holds the features nf(h, a).  After the output layer
