@@ -663,19 +663,15 @@ __device__ __forceinline__ int64_t visit(const uint32_t *perm, int64_t v)
 // most corners.  The cell lookup is monotone in the position, so every corner
 // lies in the window; a corner that did not would take the direct path.
 //
-// Window sums (WT): FP64, or (WT = int) 32-bit fixed point, which keeps the
-// precision form free of FP64 and of FP32 LDS atomics (slow on this chip).
-// In fixed point each level gets a power-of-two scale from the largest |dG|
+// Window sums are 32-bit fixed point (no FP64, and no FP32 LDS atomics, which
+// are slow on this chip).
+// Each level gets a power-of-two scale from the largest |dG|
 // of its rows in the tile: with max |dG| < 2^e every contribution w dG
 // (w <= 1) is below 2^e, at most 32 of them land on one lattice point (one
 // per vertex of the tile), so at the scale 2^(25 - e) every sum stays below
 // 2^30; each contribution is rounded to a multiple of 2^(e - 25) and the sum
 // is exact, independent of the order of the adds.
-template <typename WT> struct WinScale {
-    __device__ __forceinline__ WT enc(float v) const { return WT(v); }
-    __device__ __forceinline__ float dec(WT s) const { return (float)s; }
-};
-template <> struct WinScale<int> {
+struct WinScale {
     int k = 0;                               // the scale is 2^k (ldexp: no overflow of 2^k itself)
     // the scale of level l from its F rows of the tile's dG (all lanes call
     // it); false when they are all zero
@@ -719,14 +715,12 @@ __device__ __forceinline__ float row_bcast(float v)
     return __int_as_float(row_bcast<J>(__float_as_int(v)));
 }
 
-template <int F, int WIN_PTS, typename WT = float>
+template <int F, int WIN_PTS>
 __device__ __forceinline__ void scatter_tile(const GridView &gv, const float *dGt,
                                              const float *__restrict__ pos, const uint32_t *perm,
                                              int64_t n, int64_t t, int lane,
                                              float *__restrict__ grad, const float *lo,
-                                             const float *hi, WT *win,
-                                             const float *rec = nullptr, int rec_stride = 8,
-                                             uint32_t skip_mask = 0u)
+                                             const float *hi, int *win)
 {
     constexpr int LPV = 8 * F;              // lanes per vertex-level
     constexpr int VPI = 64 / LPV;           // vertex-levels per instruction
@@ -742,16 +736,10 @@ __device__ __forceinline__ void scatter_tile(const GridView &gv, const float *dG
 #pragma unroll
     for (int jj = 0; jj < (BC ? 1 : NJ); ++jj) {
         const int64_t v = t * 32 + (BC ? ((lane & 15) % NJ) : jj) * VPI + q;
-        if (rec) {
-            const f32x4 a = *reinterpret_cast<const f32x4 *>(rec + (size_t)(v < n ? v : n - 1) * rec_stride);
-            px[jj] = a[0]; py[jj] = a[1]; pz[jj] = a[2];
-        } else {
-            const int64_t vv = visit(perm, v < n ? v : n - 1);
-            px[jj] = pos[vv]; py[jj] = pos[n + vv]; pz[jj] = pos[2 * n + vv];
-        }
+        const int64_t vv = visit(perm, v < n ? v : n - 1);
+        px[jj] = pos[vv]; py[jj] = pos[n + vv]; pz[jj] = pos[2 * n + vv];
     }
     for (int l = 0; l < gv.n_levels; ++l) {
-        if ((skip_mask >> l) & 1u) continue;      // scattered by the binned pass
         const int D = gv.res[l];
         const uint32_t d1 = (uint32_t)D + 1u;
         const bool hashed = (gv.hashed_mask >> l) & 1u;
@@ -774,14 +762,12 @@ __device__ __forceinline__ void scatter_tile(const GridView &gv, const float *dG
             use_win = ex <= WIN_PTS && ey <= WIN_PTS && ez <= WIN_PTS &&
                       ex * ey <= WIN_PTS && ex * ey * ez <= WIN_PTS;
         }
-        WinScale<WT> sc;
-        if constexpr (std::is_same<WT, int>::value) {
-            // a level whose dG rows are all zero has nothing to scatter
-            if (use_win && !sc.template set_level<F>(dGt, l, lane)) continue;
-        }
+        WinScale sc;
+        // a level whose dG rows are all zero has nothing to scatter
+        if (use_win && !sc.set_level<F>(dGt, l, lane)) continue;
         if (use_win) {
             const int nw = ex * ey * ez * F;
-            for (int i = lane; i < nw; i += 64) win[i] = WT(0);
+            for (int i = lane; i < nw; i += 64) win[i] = 0;
             wave_lds_fence();
         }
         // corner (bx, by, bz), feature f of vertex j of the tile
@@ -824,8 +810,8 @@ __device__ __forceinline__ void scatter_tile(const GridView &gv, const float *dG
             wave_lds_fence();
             const int nw = ex * ey * ez * F;
             for (int i = lane; i < nw; i += 64) {
-                const WT s = win[i];
-                if (s != WT(0)) {
+                const int s = win[i];
+                if (s != 0) {
                     const int p = i / F, pf = i % F;
                     const int pyz = p / ex, wx = p - pyz * ex, wz = pyz / ey, wy = pyz - wz * ey;
                     unsafeAtomicAdd(grad + (size_t)entry(x0 + wx, y0 + wy, z0 + wz) * F + pf,

@@ -243,7 +243,7 @@ __global__ __launch_bounds__(256) void k_serve_train(RoundHdr *hdr, const DevReq
                 wave_lds_fence();
                 t32_to_lds<IN0 / 2>(tbuf, dG, lane);
                 wave_lds_fence();
-                scatter_tile<F, WIN_PTS, int>(gv, tbuf, io.pos, nullptr, q.n, t, lane, io.grad, lo,
+                scatter_tile<F, WIN_PTS>(gv, tbuf, io.pos, nullptr, q.n, t, lane, io.grad, lo,
                                               hi, reinterpret_cast<int *>(tbuf + IN0 * kStride));
             }
         }
