@@ -6,7 +6,7 @@
 // weight gradients (MFMA with the tile's vertices as the reduction dimension)
 // -> the tile's dG stored; then the grid scatter in kernels of its own.  The
 // gathering kernel serves the allocation-free call (its fixed scratch holds no
-// features), the FP32 form of the wide NPM-product input and the precision
+// features), the FP32 shapes that train_tile_takes leaves out and the precision
 // form's loss alone; every other gradient runs k_train_tile (k_train.hip) on
 // features encoded level by level.
 // Batches of kSortMinBatch vertices or more are visited in a spatial order

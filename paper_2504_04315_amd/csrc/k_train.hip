@@ -514,8 +514,8 @@ template <int IN_P, int HID_P, int NH, int F, bool BF, int PG = 0, bool SEL = fa
 static hipError_t run_train(npm_ctx *ctx, FusedArgs a, hipStream_t s)
 {
     using DB = DwBlocks<IN_P, HID_P, NH>;
-    if constexpr (IN_P > 32 && !BF) {
-        return hipErrorNotSupported;      // the images and their planes exceed the LDS
+    if constexpr (!BF && (IN_P > 32 || (SEL && NH >= 3))) {
+        return hipErrorNotSupported;      // train_tile_takes
     } else {
         // of W_0^T, the last segment, only the input-gradient rows are needed
         const int t_elems = a.bwd_elems - (DB::IN0 - (PG > 0 ? 32 : DB::IN0)) * HID_P;

@@ -289,6 +289,21 @@ hipError_t chunk_scatter(const Net &net, int64_t n, const float *pos, const uint
                          const float *rec, int rec_stride, const float *dgt, int rows,
                          float *grad, uint32_t level_mask, hipStream_t s);
 
+// Whether the training tile kernel on encoded features (k_train.hip) takes the
+// network; the gathering kernel (k_fused.hip) takes the others.  In FP32 the
+// weight images and planes of the wide NPM-product input exceed the LDS, and
+// the sums of the selection row beside three hidden layers the registers: 133
+// would be spilled, and around spilled registers this compiler's rewriting of
+// the matrix instructions' sums has given wrong weight gradients, so that no
+// shape that spills is built (200,001 vertices on the 16-level hash grid with
+// the selection output, spilling 490 us, gathering 506; 30,001 vertices 167 and
+// 154).
+inline bool train_tile_takes(const Net &net)
+{
+    return net.cfg.precision == NPM_PREC_BF16 ||
+           (net.mlp.in_p <= 32 && !(net.cfg.learn_selection && net.mlp.n_hidden >= 3));
+}
+
 // fused path (k_query.hip, k_fused.hip)
 // whether the fused kernels are instantiated for the network's shape (the
 // dispatch tables of k_fused.hip)

@@ -558,12 +558,8 @@ static bool use_feat(const npm_ctx *ctx, int64_t n)
 }
 
 // Whether a training batch's features are encoded level by level for the tile
-// kernel of k_train.hip: every fused shape but the FP32 form of the wide
-// NPM-product input, whose weight images and planes exceed the LDS.
-static bool train_feat(const npm_ctx *ctx)
-{
-    return ctx->net.mlp.in_p <= 32 || ctx->net.cfg.precision == NPM_PREC_BF16;
-}
+// kernel of k_train.hip.
+static bool train_feat(const npm_ctx *ctx) { return train_tile_takes(ctx->net); }
 
 static hipError_t ensure_feat(npm_ctx *ctx, int64_t n)
 {
