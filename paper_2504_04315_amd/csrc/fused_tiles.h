@@ -320,51 +320,32 @@ __device__ __forceinline__ void mlp_forward(const void *img, const float *x, flo
 
 // ------------------------------------------------------------------ head
 // The four lobes of this half-wave mapped from the raw outputs o[16], with the
-// log-sum-exp of lambda' over all eight lobes; lam (or null): the weights.
-__device__ __forceinline__ void map_half(const float *o, Lobe *L, float *lam = nullptr)
+// log-sum-exp of lambda' over all eight lobes.
+__device__ __forceinline__ void map_half(const float *o, Lobe *L)
 {
     float mx = fmaxf(fmaxf(o[3], o[7]), fmaxf(o[11], o[15]));
     mx = fmaxf(mx, xor32(mx));
-    float se = 0.0f, e[4];
+    float se = 0.0f;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        e[r] = expf(o[4 * r + 3] - mx);
-        se += e[r];
-    }
+    for (int r = 0; r < 4; ++r) se += expf(o[4 * r + 3] - mx);
     se += xor32(se);
     const float lse = mx + logf(se);
-    if (lam) {
-        const float inv = 1.0f / se;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) lam[r] = e[r] * inv;
-    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) map_lobe(o[4 * r], o[4 * r + 1], o[4 * r + 2], o[4 * r + 3], lse, L[r]);
 }
 
-// log V(w) over all eight lobes; lt[r] receives this half's log terms, resp (or
-// null) its responsibilities, each lobe's share of V.
-__device__ __forceinline__ float logpdf_half(const Lobe *L, float wx, float wy, float wz, float *lt,
-                                             float *resp = nullptr)
+// log V(w) over all eight lobes; lt[r] receives this half's log terms.
+__device__ __forceinline__ float logpdf_half(const Lobe *L, float wx, float wy, float wz, float *lt)
 {
-    float m = -INFINITY, e[4];
+    float m = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 4; ++r) { lt[r] = lobe_logterm(L[r], wx, wy, wz); m = fmaxf(m, lt[r]); }
     float s = 0.0f;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        e[r] = expf(lt[r] - m);
-        s += e[r];
-    }
+    for (int r = 0; r < 4; ++r) s += expf(lt[r] - m);
     const float mo = xor32(m), so = xor32(s);
     const float M = fmaxf(m, mo);
-    const float f = expf(m - M);
-    const float S = s * f + so * expf(mo - M);
-    if (resp) {
-        const float inv = f / S;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) resp[r] = e[r] * inv;
-    }
+    const float S = s * expf(m - M) + so * expf(mo - M);
     return M + logf(S);
 }
 
@@ -874,8 +855,11 @@ __device__ __forceinline__ TrainInputs train_inputs(const TrainIO &io, int64_t v
 // The KL-gradient head (Sec. 4.2, eq. mcgradients) of a tile: d = d loss /
 // d raw for this half-wave's four lobes, from the raw outputs o; lacc
 // accumulates -w log V (FP64) of half 0's vertices.  Returns log V at the
-// sample's direction.
-// SHARED: see lobe_grad.
+// sample's direction.  The responsibilities and the lobe weights come from the
+// log terms, as the loss does: taken from the two softmaxes' own exponentials
+// their roundings had a common sign over a batch, and the weight gradients of
+// the output layers doubled their error where one of the two was and grew by up
+// to 14 % where both were.  SHARED: see lobe_grad.
 template <bool SHARED>
 __device__ __forceinline__ float kl_head(const float *o, const TrainInputs &in, bool valid,
                                          float invN, int h, float *d, double &lacc)
@@ -884,16 +868,15 @@ __device__ __forceinline__ float kl_head(const float *o, const TrainInputs &in, 
 #pragma unroll
     for (int i = 0; i < 16; ++i) d[i] = 0.0f;
     Lobe L[4];
-    float lam[4], lt[4], resp[4];
-    map_half(o, L, SHARED ? lam : nullptr);
-    const float lv = logpdf_half(L, in.wx, in.wy, in.wz, lt, SHARED ? resp : nullptr);
+    float lt[4];
+    map_half(o, L);
+    const float lv = logpdf_half(L, in.wx, in.wy, in.wz, lt);
     if (wgt != 0.0f) {
         const float g = -wgt * invN;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            lobe_grad<SHARED>(L[r], o[4 * r], o[4 * r + 1], o[4 * r + 2],
-                              SHARED ? resp[r] : expf(lt[r] - lv),
-                              SHARED ? lam[r] : expf(L[r].loglam), g, in.wx, in.wy, in.wz, d + 4 * r);
+            lobe_grad<SHARED>(L[r], o[4 * r], o[4 * r + 1], o[4 * r + 2], expf(lt[r] - lv),
+                              expf(L[r].loglam), g, in.wx, in.wy, in.wz, d + 4 * r);
         if (h == 0) lacc -= (double)wgt * (double)lv;
     }
     return lv;

@@ -16,8 +16,19 @@
 // Split operands: x = x0 + x1 + x2 exactly (8 + 8 + 8 significand bits, each
 // remainder of a round-to-nearest BF16 conversion is exact in FP32), and the
 // six products x0 y0, x0 y1, x1 y0, x1 y1, x0 y2, x2 y0 (Henry, Tang and
-// Heinecke, 2019) leave out terms below 2^-26 of the product, accumulated in
-// FP32 over 16 terms an instruction instead of 2.
+// Heinecke, 2019) leave out at most 2^-24 of the product (2^-26 or less in 97
+// of 100), half an FP32 rounding step; adding x1 y2 and x2 y1 changed no
+// gradient's error and cost 2.5 % of a step.  What does matter is how the
+// products are summed: the matrix unit cuts an addend off at the last place of
+// the largest of an instruction's 16 products and its sum, so the five small
+// products, added to the sum of the large ones, lost their last bits each time.
+// They are summed by themselves and added once by the vector unit: in the delta
+// chain over the whole layer, in the weight gradients over a tile.  Weight
+// gradients of the 16-level network, 30,001 vertices, error against 64 bits
+// relative to the kernel with FP32 products: layers 0 to 3 1.20, 1.55, 1.19 and
+// 0.96 with one sum, 1.02, 1.05, 1.01 and 0.97 with two, the whole gradient
+// 1.15 and 1.00 (0.97 to 0.99 on other networks and sizes); a step of 2^20
+// vertices takes 2 % longer for it.
 //
 // A wave is on its own from tile to tile: it keeps all weight-gradient blocks
 // in accumulators (192 registers of the 512 a wave has at one per SIMD) and
@@ -97,15 +108,16 @@ __device__ __forceinline__ f32x16 zero16()
 }
 
 // y (M wide) = W^T d for the planes d of a K-wide vector; img: plane p of the
-// packed BF16 image of W^T at img + p * stride (device_math.h's layout).
+// packed BF16 image of W^T at img + p * stride (device_math.h's layout).  The
+// largest products and the others have sums of their own (see the top).
 template <int K, int M, bool BF>
 __device__ __forceinline__ void chain_layer(const __bf16 *img, int stride, const Planes<K / 2, BF> &d,
                                             float *y, int lane)
 {
     constexpr int NB = M / 32, NS = K / 16, P = kPlanes<BF>;
-    f32x16 acc[NB];
+    f32x16 acc[NB], low[NB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) acc[b] = zero16();
+    for (int b = 0; b < NB; ++b) acc[b] = low[b] = zero16();
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         bf16x8 A[NB][P];
@@ -118,14 +130,16 @@ __device__ __forceinline__ void chain_layer(const __bf16 *img, int stride, const
 #pragma unroll
         for (int i = 0; i < Products<BF>::N; ++i)
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
-                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[b][Products<BF>::pa(i)],
-                                                                 d.op(Products<BF>::pb(i), s), acc[b], 0, 0, 0);
+            for (int b = 0; b < NB; ++b) {
+                f32x16 &q = i + 1 < Products<BF>::N ? low[b] : acc[b];
+                q = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[b][Products<BF>::pa(i)],
+                                                            d.op(Products<BF>::pb(i), s), q, 0, 0, 0);
+            }
     }
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) y[16 * b + v] = acc[b][v];
+        for (int v = 0; v < 16; ++v) y[16 * b + v] = BF ? acc[b][v] : acc[b][v] + low[b][v];
 }
 
 // A 32-row block with the tile's 32 vertices as the reduction dimension: lane
@@ -364,16 +378,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             for (int c = 0; c < NBI; ++c) {
                 Rows<BF> ri;
                 ri.load(id, inp, c);
+if constexpr (BF) {
 #pragma unroll
-                for (int s = 0; s < 2; ++s)
-#pragma unroll
-                    for (int i = 0; i < Products<BF>::N; ++i)
+                    for (int s = 0; s < 2; ++s)
 #pragma unroll
                         for (int b = 0; b < NBO; ++b) {
                             f32x16 &q = acc[DB::first(L) + b * NBI + c];
-                            q = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rd[b].k[s][Products<BF>::pa(i)],
-                                                                        ri.k[s][Products<BF>::pb(i)], q, 0, 0, 0);
+                            q = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rd[b].k[s][0], ri.k[s][0], q, 0, 0, 0);
                         }
+                } else {
+#pragma unroll
+                    for (int b = 0; b < NBO; ++b) {
+                        f32x16 &q = acc[DB::first(L) + b * NBI + c];
+                        f32x16 low = zero16();
+#pragma unroll
+                        for (int i = 0; i + 1 < Products<BF>::N; ++i)
+#pragma unroll
+                            for (int s = 0; s < 2; ++s)
+                                low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                    rd[b].k[s][Products<BF>::pa(i)], ri.k[s][Products<BF>::pb(i)], low, 0, 0, 0);
+                        q += low;
+#pragma unroll
+                        for (int s = 0; s < 2; ++s)
+                            q = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rd[b].k[s][0], ri.k[s][0], q, 0, 0, 0);
+                        // one block at a time: the small sums of two do not fit beside the rest
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
             }
         };
         {
