@@ -130,7 +130,7 @@ __device__ __forceinline__ void block_exclusive_scan(const uint32_t *__restrict_
     if (2 * t + 1 < m) out[2 * t + 1] = e + x0;
 }
 
-// Clears the bins' totals and the batch's largest |dG| after them.
+// Clears the bins' totals and the two words of the batch after them.
 __global__ void k_bin_zero(uint32_t *__restrict__ tot, int words)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -144,7 +144,8 @@ __global__ void k_bin_zero(uint32_t *__restrict__ tot, int words)
 // chunk's runs lie together, one line request for 16 of them.
 //
 // Per chunk: {offset within the bin, items} of every bin into run[chunk][bin],
-// and the largest |dG| into tot[nbins], which scales the fixed-point reduce.
+// the largest finite |dG| into tot[nbins], which scales the fixed-point reduce,
+// and into tot[nbins + 1] whether a binned dG is infinite or NaN.
 template <int F>
 __global__ __launch_bounds__(kBinChunk) void k_bin_count(GridDesc g, BinDesc bd, int64_t n,
                                                          const float *__restrict__ pos,
@@ -162,14 +163,14 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_count(GridDesc g, BinDesc bd,
     constexpr int NC = 4, HS = kBinMaxBins + 1;
     __shared__ uint32_t hist[NC * HS];
     __shared__ int s_lv[NPM_MAX_LEVELS], s_res[NPM_MAX_LEVELS];
-    __shared__ uint32_t s_max;
+    __shared__ uint32_t s_max, s_odd;
     int j0, j1;
     level_share(bd.nb, j0, j1);
     const int k0 = j0 * bd.ns, nk = (j1 - j0) * bd.ns;
     for (int k = threadIdx.x; k < nk; k += kBinChunk)
 #pragma unroll
         for (int r = 0; r < NC; ++r) hist[r * HS + k] = 0u;
-    if (threadIdx.x == 0) s_max = 0u;
+    if (threadIdx.x == 0) s_max = s_odd = 0u;
     if (threadIdx.x < NPM_MAX_LEVELS) {
         s_lv[threadIdx.x] = bd.lv[threadIdx.x];
         s_res[threadIdx.x] = g.res[threadIdx.x];
@@ -177,7 +178,8 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_count(GridDesc g, BinDesc bd,
     __syncthreads();
     const int64_t s = blockIdx.x * (int64_t)kBinChunk + threadIdx.x;
     uint32_t *hc = hist + (threadIdx.x & (NC - 1)) * HS;
-    float dmax = 0.0f;      // largest |dG| the chunk bins (bounds every item)
+    uint32_t dmax = 0u;     // largest finite |dG| the chunk bins (bounds every finite item): its bits
+    bool odd = false;       // an infinite or NaN one among them
     if (s < n) {
         float p[3];
         slot_position(pos, perm, rec, rec_stride, n, s, p);
@@ -190,7 +192,13 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_count(GridDesc g, BinDesc bd,
             if (j + 1 < j1) slot_dg<F>(dgt, rows, s, s_lv[j + 1], dn);
             if (!any) continue;
 #pragma unroll
-            for (int f = 0; f < F; ++f) dmax = fmaxf(dmax, fabsf(d[f]));
+            for (int f = 0; f < F; ++f) {
+                // non-negative floats order as their bit patterns
+                const uint32_t u = __float_as_uint(d[f]) & 0x7fffffffu;
+                const bool finite = u < 0x7f800000u;
+                dmax = max(dmax, finite ? u : 0u);
+                odd |= !finite;
+            }
             int c[3];
             float fr[3];
 #pragma unroll
@@ -204,8 +212,8 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_count(GridDesc g, BinDesc bd,
             }
         }
     }
-    // non-negative floats order as their bit patterns
-    atomicMax(&s_max, __float_as_uint(dmax));
+    atomicMax(&s_max, dmax);
+    if (odd) s_odd = 1u;
     __syncthreads();
     for (int k = threadIdx.x; k < nk; k += kBinChunk) {
         uint32_t c = 0u;
@@ -215,6 +223,7 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_count(GridDesc g, BinDesc bd,
         run[(size_t)blockIdx.x * bd.nbins + k0 + k] = make_uint2(o, c);
     }
     if (threadIdx.x == 0 && s_max) atomicMax(&tot[bd.nbins], s_max);
+    if (threadIdx.x == 0 && s_odd) atomicMax(&tot[bd.nbins + 1], 1u);
 }
 
 template <int F>
@@ -349,11 +358,12 @@ __global__ __launch_bounds__(kBinChunk) void k_bin_place(GridDesc g, BinDesc bd,
 // read-add-write of the slice into the gradient.  The sums are FP64 (LDS
 // FP64 atomic adds run several times faster than FP32 ones on this chip, and
 // the wider sum rounds once, when it is added to the FP32 gradient), or, in
-// the precision form (FIXED), 64-bit fixed point: with every corner value
-// below the batch's largest |dG|, M < 2^e, and 2c corner values in the bin of
+// the precision form (FIXED), 64-bit fixed point: with every finite corner value
+// below the batch's largest finite |dG|, M < 2^e, and 2c corner values in the bin of
 // c items (2c <= 2^b), the scale 2^(62 - e - b) keeps every entry's sum below
 // 2^62; each value is rounded to a multiple of 2^(e + b - 62) (below 1e-12 of
-// M for any bin of at most 2^22 items) and the sum is exact in any order.
+// M for any bin of at most 2^22 items) and the sum is exact in any order.  An
+// infinite or NaN value goes to the gradient itself, as a float.
 //
 // Bound by the items' 16 bytes and the LDS adds, which a batch of loads
 // followed by its adds paid one after the other: the next batch is in flight
@@ -377,10 +387,13 @@ __global__ __launch_bounds__(kBinReduceThreads) void k_bin_reduce(GridDesc g, Bi
     const int nf = (int)S * F;
     const uint64_t beg = base[k];
     const uint64_t end = min(beg + tot[k], (uint64_t)bd.cap);
+    float *dst = grad + ((size_t)g.offset[bd.lv[j]] + (size_t)slice * S) * F;
     int kx = 0;                                  // fixed point: the scale is 2^kx
+    bool odd = false;                            // the batch has infinite or NaN values (uniform)
     if constexpr (FIXED) {
         const float M = __uint_as_float(tot[bd.nbins]);
-        if (!(M > 0.0f) || end <= beg) return;   // nothing to add (block-uniform)
+        odd = tot[bd.nbins + 1] != 0u;
+        if (!(M > 0.0f || odd) || end <= beg) return;   // nothing to add (block-uniform)
         int e;
         frexpf(M, &e);                           // M < 2^e
         const uint64_t c = 2 * (end - beg);                            // corner values
@@ -403,6 +416,11 @@ __global__ __launch_bounds__(kBinReduceThreads) void k_bin_reduce(GridDesc g, Bi
             const float w0 = 1.0f - fx;
 #pragma unroll
             for (int f = 0; f < F; ++f) {
+                if (FIXED && odd && !isfinite(v[f])) {
+                    unsafeAtomicAdd(dst + (size_t)e0 * F + f, w0 * v[f]);
+                    unsafeAtomicAdd(dst + (size_t)e1 * F + f, fx * v[f]);
+                    continue;
+                }
                 add1(f * S + e0, w0 * v[f]);
                 add1(f * S + e1, fx * v[f]);
             }
@@ -457,12 +475,14 @@ __global__ __launch_bounds__(kBinReduceThreads) void k_bin_reduce(GridDesc g, Bi
         add(e[0], fx[0], v[0]);
     }
     __syncthreads();
-    float *dst = grad + ((size_t)g.offset[bd.lv[j]] + (size_t)slice * S) * F;
     for (int i2 = threadIdx.x; i2 < nf; i2 += NT) {
         const int at = (i2 % F) * (int)S + i2 / F;
         if constexpr (FIXED) {
             const long long a = (long long)acc[at];
-            if (a != 0) dst[i2] += ldexpf(__ll2float_rn(a), -kx);
+            if (a == 0) continue;
+            const float v = ldexpf(__ll2float_rn(a), -kx);
+            if (odd) unsafeAtomicAdd(dst + i2, v);     // beside this block's float adds
+            else dst[i2] += v;
         } else {
             const double a = acc[at];
             if (a != 0.0) dst[i2] += (float)a;
@@ -503,14 +523,14 @@ bool bin_plan(const npm_ctx *ctx, int64_t n, bool ordered, BinDesc *out)
     return true;
 }
 
-// the bins' totals and the batch's largest |dG| (bin_clear_words, zero before
-// the pass), the bins' starts, then the chunks' runs (two words per bin and chunk)
-int bin_clear_words(const BinDesc &b) { return b.nbins + 1; }
+// the bins' totals and the batch's two words (bin_clear_words, zero before the
+// pass), the bins' starts, then the chunks' runs (two words per bin and chunk)
+int bin_clear_words(const BinDesc &b) { return b.nbins + 2; }
+static size_t bin_head_words(const BinDesc &b) { return 2 * (size_t)b.nbins + 2; }   // even: uint2 runs
 
 size_t bin_count_words(const BinDesc &b)
 {
-    const size_t head = (2 * (size_t)b.nbins + 2) / 2 * 2;
-    return head + 2 * (size_t)b.nbins * (size_t)b.n_chunks;
+    return bin_head_words(b) + 2 * (size_t)b.nbins * (size_t)b.n_chunks;
 }
 
 // items: cap records of (key, x fraction, F FP32 values)
@@ -525,8 +545,8 @@ static void launch_bins(const GridDesc &g, const BinDesc &b, int64_t n, const fl
                         int rows, float *grad, uint32_t *cnt, uint32_t *items, int phase,
                         bool fixed, hipStream_t s)
 {
-    uint32_t *tot = cnt, *base = cnt + b.nbins + 1;
-    uint2 *run = reinterpret_cast<uint2 *>(cnt + (2 * (size_t)b.nbins + 2) / 2 * 2);
+    uint32_t *tot = cnt, *base = cnt + bin_clear_words(b);
+    uint2 *run = reinterpret_cast<uint2 *>(cnt + bin_head_words(b));
     // a chunk's levels go to one block, or are shared by several where the
     // chunks alone are fewer than two blocks a CU (32,771 vertices, 12 levels:
     // place 37 -> 10 us; 100,003 vertices, 10 levels: 36 -> 26)
@@ -534,7 +554,7 @@ static void launch_bins(const GridDesc &g, const BinDesc &b, int64_t n, const fl
     const dim3 grid((unsigned)b.n_chunks, (unsigned)gy);
     switch (phase) {
     case 0:
-        hipLaunchKernelGGL(k_bin_zero, dim3((b.nbins + 256) / 256), dim3(256), 0, s, tot,
+        hipLaunchKernelGGL(k_bin_zero, dim3((bin_clear_words(b) + 255) / 256), dim3(256), 0, s, tot,
                            bin_clear_words(b));
         break;
     case 1:

@@ -1,0 +1,94 @@
+"""A vertex whose gradient is not finite marks the grid entries of its own corners
+(infinite or NaN) and no others, whichever scatter its levels take: the binned
+pass (FP64 sums, or fixed point in the precision form) as the chunked one, in a
+training call and in a serving round.  The other entries stay what they are
+without the vertex, to 1e-5 of the gradient's largest entry (the FP32
+tolerance)."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+from paper_2504_04315_amd import npm as B
+from paper_2504_04315_amd import serve as S
+from paper_2504_04315_amd import workload as W
+from test_gpu_parity import dev
+
+pytestmark = pytest.mark.gpu
+
+N = 20011          # the smallest batches that are binned by themselves begin at 20,000
+
+
+def _batch():
+    b = W.make_batch("surface", N, seed=63)
+    return b, (777, 12345)
+
+
+def _spoil(b, at):
+    b.dir[0, at[0]] = np.nan                  # a gradient of NaN
+    b.radiance[at[1]], b.pdf[at[1]] = 3e38, 1e-3   # a sample weight beyond the floats
+    return b
+
+
+def _marked(model, torch, b, at):
+    """Flags of the grid parameters of the vertices' corners."""
+    lay, F = model.layout, model.cfg.feat_per_level
+    idx = model.corner_index(dev(torch, b.pos)).cpu().numpy().astype(np.int64)[:, :, list(at)]
+    flag = np.zeros(lay.grid_params, dtype=bool)
+    for f in range(F):
+        flag[idx.reshape(-1) * F + f] = True
+    return flag
+
+
+def _check(got, ref, flag, scale):
+    bad = ~np.isfinite(got)
+    assert np.all(np.isfinite(ref))
+    assert np.array_equal(bad, flag), (bad.sum(), flag.sum(), (bad & ~flag).sum())
+    assert np.max(np.abs(got[~bad] - ref[~bad])) <= 1e-5 * scale
+
+
+@pytest.mark.parametrize("order", [B.ORDER_NONE, B.ORDER_SPATIAL])
+@pytest.mark.parametrize("scatter", [B.SCATTER_ATOMIC, B.SCATTER_BINNED, B.SCATTER_AUTO])
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+def test_marks_its_own_corners(prec, scatter, order):
+    import torch
+    net = replace(W.CFG5, precision=prec)
+    model = B.NPM(B.make_config(net, exec_mode=B.EXEC_FUSED, batch_order=order,
+                                scatter_mode=scatter))
+    model.set_state(np.random.default_rng(52).normal(0, 0.3, model.n_params).astype(np.float32))
+    gp = model.layout.grid_params
+    res = []
+    b, at = _batch()
+    zero = b.radiance.copy()
+    for spoil in (False, True):
+        if spoil:
+            b.radiance[:] = zero
+            _spoil(b, at)
+        else:
+            b.radiance[list(at)] = 0.0        # the batch without the two vertices
+        g = torch.zeros(model.n_params, dtype=torch.float32, device="cuda")
+        model.backward(*[dev(torch, a) for a in (b.pos, b.dir, b.radiance, b.pdf)], grad=g)
+        res.append(g.cpu().numpy().astype(np.float64)[:gp])
+    _check(res[1], res[0], _marked(model, torch, b, at), np.max(np.abs(res[0])))
+    model.close()
+
+
+def test_serving_round_marks_its_own_corners():
+    import torch
+    cfg = B.make_config(W.CFG5)
+    srv = S.Server(budget_bytes=8 << 30, max_sessions=4)
+    model = B.NPM(cfg)
+    gp, n_params = model.layout.grid_params, model.n_params
+    res = []
+    for spoil in (False, True):
+        b, at = _batch()
+        if spoil:
+            _spoil(b, at)
+        else:
+            b.radiance[list(at)] = 0.0
+        sid = srv.create_session(cfg)
+        srv.wait(srv.submit_train(sid, *[dev(torch, a) for a in (b.pos, b.dir, b.radiance, b.pdf)]))
+        res.append(srv.session_state(sid, n_params, B.STATE_ADAM_M).astype(np.float64)[:gp])
+    _check(res[1], res[0], _marked(model, torch, b, at), np.max(np.abs(res[0])))
+    model.close()
+    srv.close()
