@@ -37,6 +37,8 @@ struct FusedArgs {
     const void *feat;        // level-major grid features of the batch (k_encode.hip)
     const __bf16 *img_t;     // packed BF16 image of W^T (the backward image), and the two
     const __bf16 *img_split; // further planes of its three-way split (FP32 training)
+    const float *mlp;        // the flat FP32 MLP weights (backward)
+    float *grad_mlp;         // and their gradient
 };
 
 inline FusedArgs fused_args(npm_ctx *ctx, int64_t n, const float *pos)

@@ -422,6 +422,8 @@ hipError_t fused_backward(npm_ctx *ctx, int64_t n, const float *pos, const float
     const bool b16 = ctx->net.cfg.precision == NPM_PREC_BF16;
     a.img_t = (const __bf16 *)ctx->mlp_img16 + ctx->net.mlp.fwd_elems;
     a.img_split = (const __bf16 *)ctx->mlp_split;
+    a.mlp = ctx->params + ctx->net.lay.grid_params;
+    a.grad_mlp = grad ? grad + ctx->net.lay.grid_params : nullptr;
     hipError_t e = hipSuccess;
     int tok;
     if (feat && grad) {

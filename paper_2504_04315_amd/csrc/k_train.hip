@@ -208,6 +208,62 @@ template <int IN_P, int HID_P, int NH> struct DwBlocks {
     static constexpr int total() { return first(-1); }
 };
 
+// A vertex with an infinite or NaN feature, or derivative of the head, takes no
+// part in a tile's products: the split has no form for such a value, and the
+// identity product would hand it to the other 31 rows of its block.  The tile
+// loop takes it as zero, leaves kOddInput or kOddHead in the first row of its dG,
+// and at the end of the block, the accumulators written, the wave evaluates such
+// vertices one at a time (OddVertex), so that they mark the gradient entries they
+// belong to -- those of the units that are on -- and no others.  The checks cost
+// a finite batch 0.3 to 1 % of a step (2 % at 16,384 vertices).
+constexpr uint32_t kOddInput = 0x7fc0dd01u, kOddHead = 0x7fc0dd02u;      // NaNs no sum makes
+// the lanes with an infinite or NaN value among R
+template <int R> __device__ __forceinline__ uint64_t odd_lanes(const float *x, float z = 0.0f)
+{
+    z *= 0.0f;
+#pragma unroll
+    for (int i = 0; i < R; ++i) z = fmaf(x[i], 0.0f, z);
+    return __ballot(z != z);
+}
+
+// FP32 with three hidden layers or the selection sums: the first layer's
+// activations wait in LDS (8 KB a wave), and the input features are read again
+// for their weight gradient.
+constexpr bool parks(bool bf, int hidden, bool sel) { return !bf && (hidden >= 3 || sel); }
+
+// One vertex's layers by a wave, a unit per lane, weights read from memory as
+// the form uses them (rounded to BF16 in the precision form).
+template <bool BF> struct OddVertex {
+    const float *w;                            // flat MLP weights
+    float *g;                                  // their gradient
+    int lane;
+
+    __device__ __forceinline__ static float used(float x) { return BF ? (float)(__bf16)x : x; }
+    // row `lane` of the layer at off times in
+    __device__ __forceinline__ float forward(int64_t off, int rows, int cols, const float *in) const
+    {
+        float s = 0.0f;
+        if (lane < rows)
+            for (int i = 0; i < cols; ++i) s = fmaf(used(w[off + (int64_t)lane * cols + i]), used(in[i]), s);
+        return s;
+    }
+    // the layer's weight gradient
+    __device__ __forceinline__ void weights(int64_t off, int rows, int cols, const float *d, const float *in) const
+    {
+        for (int o = 0; o < rows; ++o)
+            for (int i = lane; i < cols; i += 64)
+                unsafeAtomicAdd(g + off + (int64_t)o * cols + i, used(d[o]) * used(in[i]));
+    }
+    // column `lane` of the layer times d
+    __device__ __forceinline__ float back(int64_t off, int rows, int cols, const float *d) const
+    {
+        float s = 0.0f;
+        if (lane < cols)
+            for (int o = 0; o < rows; ++o) s = fmaf(used(w[off + (int64_t)o * cols + lane]), used(d[o]), s);
+        return s;
+    }
+};
+
 }  // namespace
 
 // SEL: the network has the selection output (k_fused.hip); the row's gradient is
@@ -238,9 +294,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         for (int i = threadIdx.x; i < HID_P; i += 256) s_wsel[i] = i < a.width ? a.wsel[i] : 0.0f;
     __syncthreads();
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, h = lane >> 5;
-    // FP32, three hidden layers: the first one's activations wait in LDS (8 KB a
-    // wave), and the input features are read again for their weight gradient
-    constexpr bool PARK = !BF && NH >= 3;
+    constexpr bool PARK = parks(BF, NH, SEL);
     f32x4 *park = reinterpret_cast<f32x4 *>(bwd + P * t_elems) + wave * (HID_P / 8 * 64) + lane;
     const Identity id(lane);
     const TrainIO io{a.n, a.pos, a.dir, a.rad, a.spdf, a.grad, a.invN, a.perm, a.rec, a.aux,
@@ -253,6 +307,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
     for (int i = 0; i < (SEL ? HID_P / 2 : 1); ++i) selacc[i] = 0.0f;
     double lacc = 0.0, lsel = 0.0;
+    bool any_odd = false;
     const int64_t n = a.n, ntiles = (n + 31) / 32;
     const int64_t nwaves = (int64_t)gridDim.x * 4;
     auto slot = [&](int64_t t) {
@@ -267,7 +322,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         in_next = train_inputs(io, slot(t), slot(t));
     }
     for (; t < ntiles; t += nwaves) {
-        const bool valid = t * 32 + (lane & 31) < n;
+        bool valid = t * 32 + (lane & 31) < n;
         const TrainInputs in = in_next;
         float x[IN0 / 2];
         feat_take<IN_P, ING, BF>(fw, gf, h, x);
@@ -278,6 +333,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             load_aux(io.rec, io.rec_stride, io.aux, n, slot(t), slot(t), a7);
             aux_fill<IN_P, ProductShape<PG>::GF, ProductShape<PG>::SHD>(h, a7, x);
         }
+        const uint64_t odd_in = odd_lanes<IN_P / 2>(x);
+        uint32_t odd = (uint32_t)odd_in | (uint32_t)(odd_in >> 32);
+        const bool odd_x = (odd >> (lane & 31)) & 1u;
+        valid = valid && !odd_x;
+#pragma unroll
+        for (int i = 0; i < IN_P / 2; ++i) x[i] = odd_x ? 0.0f : x[i];
         // the next tile's inputs, in flight during this one
         if (t + nwaves < ntiles) {
             feat_load<ING, BF>(a.feat, gf, n, slot(t + nwaves), h, fw);
@@ -342,6 +403,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 }
             }
         }
+        const uint64_t odd_out = odd_lanes<16>(d, ds);
+        odd |= (uint32_t)odd_out | (uint32_t)(odd_out >> 32);
+        const bool is_odd = (odd >> (lane & 31)) & 1u;
+        any_odd |= odd != 0u;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) d[i] = is_odd ? 0.0f : d[i];
+        if constexpr (SEL) ds = is_odd ? 0.0f : ds;
         // hidden unit i of layer li is on / the value its weight gradient takes
         auto on = [&](int li, int i) {
             if constexpr (BF) {
@@ -460,6 +528,7 @@ if constexpr (BF) {
             dp.set(dh);
             float dG[DGR / 2];
             chain_layer<HID_P, DGR, BF>(im, t_elems, dp, dG, lane);
+            dG[0] = is_odd ? __uint_as_float(odd_x ? kOddInput : kOddHead) : dG[0];
             float *dst = a.dg_tiles + (size_t)t * IN0 * 32 + (lane & 31) + 4 * h * 32;
 #pragma unroll
             for (int q = 0; q < DGR / 2; ++q) dst[nf(0, q) * 32] = dG[q];
@@ -468,28 +537,13 @@ if constexpr (BF) {
                     FeatWords<ING, BF> again;
                     feat_load<ING, BF>(a.feat, gf, n, slot(t), h, again);
                     feat_take<IN_P, ING, BF>(again, gf, h, x);
+#pragma unroll
+                    for (int i = 0; i < IN_P / 2; ++i) x[i] = odd_x ? 0.0f : x[i];
                 }
                 xp.set(x);
             }
             weight_gradient(std::integral_constant<int, 0>{}, dp, xp);
         }
-    }
-    // ---- loss partials of the block (FP64)
-    auto block_sum = [&](double v) {
-        __syncthreads();
-        red[threadIdx.x] = v;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-            __syncthreads();
-        }
-        return red[0];
-    };
-    const double lsum = block_sum(lacc);
-    if (threadIdx.x == 0) a.partials[blockIdx.x] = lsum;
-    if constexpr (SEL) {
-        const double ssum = block_sum(lsel);
-        if (threadIdx.x == 0) a.partials_sel[blockIdx.x] = ssum;
     }
     // ---- the waves' weight gradients meet in LDS (the images are no longer
     // read), one 32x32 block of 1,024 floats after the other, and go out in the
@@ -538,6 +592,118 @@ if constexpr (BF) {
             out[row + threadIdx.x] = v;
         }
     }
+    // ---- the wave's vertices that are not finite
+    __syncthreads();
+    if (any_odd) {
+        float *vin = reinterpret_cast<float *>(smem) + wave * 512, *vd = vin + 96, *va = vin + 160;
+        const OddVertex<BF> ov{a.mlp, a.grad_mlp, lane};
+        const int width = a.width, n_in = a.n_in;
+        const int64_t out_off = (int64_t)width * n_in + (int64_t)(NH - 1) * width * width;
+#pragma unroll 1
+        for (int64_t tt = blockIdx.x * (int64_t)4 + wave; tt < ntiles; tt += nwaves) {
+            float *col = a.dg_tiles + (size_t)tt * IN0 * 32;
+            const uint32_t mark = __float_as_uint(col[lane & 31]);
+            uint32_t todo = (uint32_t)__ballot(mark == kOddInput || mark == kOddHead);
+            if (n - tt * 32 < 32) todo &= (1u << (n - tt * 32)) - 1u;
+#pragma unroll 1
+            for (; todo; todo &= todo - 1u) {
+                const int j = __builtin_ctz(todo);
+                const int64_t v = tt * 32 + j;
+                const bool input = __shfl((int)mark, j, 64) == (int)kOddInput;
+                // every lane loads the vertex; lane 0 and lane 32 hold its halves
+                FeatWords<ING, BF> f;
+                feat_load<ING, BF>(a.feat, gf, n, v, h, f);
+                float x[IN_P / 2];
+                feat_take<IN_P, ING, BF>(f, gf, h, x);
+                if constexpr (PG > 0) {
+                    float a7[7];
+                    load_aux(io.rec, io.rec_stride, io.aux, n, v, v, a7);
+                    aux_fill<IN_P, ProductShape<PG>::GF, ProductShape<PG>::SHD>(h, a7, x);
+                }
+                wave_lds_fence();
+                if ((lane & 31) == 0)
+#pragma unroll
+                    for (int i = 0; i < IN_P / 2; ++i) vin[nf(h, i)] = x[i];
+                wave_lds_fence();
+                float y = fmaxf(ov.forward(0, width, n_in, vin), 0.0f);
+                va[lane] = y;
+                wave_lds_fence();
+                for (int li = 1; li < NH; ++li) {
+                    y = fmaxf(ov.forward((int64_t)width * n_in + (int64_t)(li - 1) * width * width, width, width, va + (li - 1) * 64), 0.0f);
+                    va[li * 64 + lane] = y;
+                    wave_lds_fence();
+                }
+                vd[lane] = ov.forward(out_off, 32, width, va + (NH - 1) * 64);
+                wave_lds_fence();
+                float o[16], d[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[i] = vd[nf(h, i)];
+                const TrainInputs in = train_inputs(io, v, v);
+                double l = 0.0;
+                const float lv = kl_head<!BF>(o, in, true, io.invN, h, d, l);
+                if (input && lane == 0) lacc += l;
+                float ds = 0.0f;
+                if constexpr (SEL) {
+                    float cp = lane < width ? s_wsel[lane] * y : 0.0f;
+#pragma unroll
+                    for (int m = 1; m < 64; m <<= 1) cp += __shfl_xor(cp, m, 64);
+                    const float wgt = sample_weight(in.rad, in.spdf);
+                    if (wgt != 0.0f && io.bsdf) {
+                        const float pb = io.bsdf[visit(io.perm, v)];
+                        if (bsdf_valid(pb)) {
+                            const float lpc = select_term(cp, pb, lv, -wgt * io.invN, ds);
+                            if (input && lane == 0) lsel -= (double)wgt * (double)lpc;
+                        }
+                    }
+                }
+                wave_lds_fence();
+                if ((lane & 31) == 0)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) vd[nf(h, i)] = d[i];
+                wave_lds_fence();
+                // from the output layer down: weights, then the delta through
+                // the units that are on
+                int64_t off = out_off;
+                int rows = 32;
+                for (int li = NH - 1; li >= 0; --li) {
+                    const float *act = va + li * 64;
+                    ov.weights(off, rows, width, vd, act);
+                    float s = ov.back(off, rows, width, vd);
+                    if constexpr (SEL)
+                        if (li == NH - 1 && lane < width) {
+                            unsafeAtomicAdd(a.grad_mlp + off + 32 * (int64_t)width + lane, ds * act[lane]);
+                            s = fmaf(ds, s_wsel[lane], s);
+                        }
+                    const float dn = act[lane] > 0.0f ? s : 0.0f;
+                    wave_lds_fence();
+                    vd[lane] = dn;
+                    wave_lds_fence();
+                    rows = width;
+                    off -= li > 0 ? (int64_t)width * width : (int64_t)width * n_in;
+                }
+                ov.weights(0, width, n_in, vd, vin);
+                const float s = ov.back(0, width, n_in, vd);
+                if (lane < DGR) col[lane * 32 + j] = lane < n_in ? s : 0.0f;
+            }
+        }
+    }
+    // ---- loss partials of the block (FP64)
+    auto block_sum = [&](double v) {
+        __syncthreads();
+        red[threadIdx.x] = v;
+        __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+            __syncthreads();
+        }
+        return red[0];
+    };
+    const double lsum = block_sum(lacc);
+    if (threadIdx.x == 0) a.partials[blockIdx.x] = lsum;
+    if constexpr (SEL) {
+        const double ssum = block_sum(lsel);
+        if (threadIdx.x == 0) a.partials_sel[blockIdx.x] = ssum;
+    }
 }
 
 // ------------------------------------------------------------------ launch
@@ -552,7 +718,7 @@ static hipError_t run_train(npm_ctx *ctx, FusedArgs a, hipStream_t s)
         const int t_elems = a.bwd_elems - (DB::IN0 - (PG > 0 ? 32 : DB::IN0)) * HID_P;
         const int fwd_bytes = a.fwd_elems * (BF ? 2 : 4);
         const size_t lds = std::max<size_t>((size_t)fwd_bytes + (size_t)kPlanes<BF> * t_elems * 2 +
-                                                (!BF && NH >= 3 ? 4 * HID_P / 2 * 64 * 4 : 0),
+                                                (parks(BF, NH, SEL) ? 4 * HID_P / 2 * 64 * 4 : 0),
                                             (size_t)DB::total() * 4096);
         if (lds > kLdsBytes) return hipErrorInvalidValue;
         auto k = k_train_tile<IN_P, HID_P, NH, F, BF, PG, SEL>;

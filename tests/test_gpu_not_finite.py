@@ -92,3 +92,73 @@ def test_serving_round_marks_its_own_corners():
     _check(res[1], res[0], _marked(model, torch, b, at), np.max(np.abs(res[0])))
     model.close()
     srv.close()
+
+
+SHAPES = {"production": replace(W.CFG5, log2_table=13, max_res=300), "paper": W.PAPER, "dense4": W.CFG1,
+          "tiny": W.TINY, "f1": replace(W.CFG5, n_levels=19, feat=1, max_res=200, log2_table=14, n_hidden=2),
+          "product": replace(W.CFG2P, log2_table=13, max_res=300), "select": W.PAPERS, "selecttiny": W.TINYS}
+CASES = [(k, p) for k in SHAPES for p in ("fp32", "bf16")]
+
+
+@pytest.mark.parametrize("name,prec", CASES, ids=["-".join(c) for c in CASES])
+def test_marks_the_weights_it_belongs_to(name, prec):
+    """The weight and grid gradients that are infinite or NaN beside a vertex
+    that is not finite -- its direction, its weight, the features of its corners
+    -- are those of the gathering kernel (of the staged path on a selection
+    network, the gathering one on its precision form's mixture), and the finite
+    ones are equal to the tolerance of the form."""
+    import torch
+    net, n = replace(SHAPES[name], precision=prec), 1025
+    kw = dict(exec_mode=B.EXEC_FUSED, batch_order=B.ORDER_NONE)
+    model = B.NPM(B.make_config(net, **kw))
+    rng = np.random.default_rng(7)
+    p = rng.normal(0, 0.3, model.n_params).astype(np.float32)
+    b = W.make_batch("surface", n, seed=64)
+    aux = W.make_aux(b, 64) if net.sh_degree else None
+    bsdf = dev(torch, W.make_bsdf(b, 64)) if net.select else None
+    idx = model.corner_index(dev(torch, b.pos)).cpu().numpy().astype(np.int64)
+    other = model
+    if net.select:
+        other = B.NPM(B.make_config(replace(net, precision="fp32"), exec_mode=B.EXEC_STAGED))
+
+    def grads(batch, params):
+        args = [dev(torch, a) for a in (batch.pos, batch.dir, batch.radiance, batch.pdf)]
+        out = []
+        for m, plain in ((model, True), (other, False)):
+            m.set_state(params)
+            g = torch.zeros(m.n_params, dtype=torch.float32, device="cuda")
+            loss = torch.zeros(2, dtype=torch.float64, device="cuda")
+            if net.select:
+                m.backward_select(*args, bsdf, grad=g, loss=loss)
+            else:
+                ax = None if aux is None else dev(torch, aux)
+                (m.backward if plain else m.backward_static)(*args, grad=g, loss=loss, aux=ax)
+            out.append((g.cpu().numpy().astype(np.float64), float(loss[0])))
+        return out
+
+    def spoil_dir(b, p):
+        b.dir[1, [3, n - 1]] = np.nan
+
+    def spoil_weight(b, p):
+        b.radiance[[40, 500]], b.pdf[[40, 500]] = 3e38, 1e-3
+
+    def spoil_feature(value):
+        def f(b, p):
+            p[idx[0, 5, 700] * net.feat] = value
+        return f
+    for label, spoil in (("none", lambda b, p: None), ("direction", spoil_dir), ("weight", spoil_weight),
+                         ("feature nan", spoil_feature(np.nan)), ("feature inf", spoil_feature(np.inf))):
+        bb, pp = W.make_batch("surface", n, seed=64), p.copy()
+        spoil(bb, pp)
+        print(name, prec, label, flush=True)
+        (got, lg), (ref, lr) = grads(bb, pp)
+        assert np.isfinite(lg) == np.isfinite(lr), (label, lg, lr)
+        bad = ~np.isfinite(ref)
+        assert label == "none" or bad.any()
+        assert np.array_equal(~np.isfinite(got), bad), (label, (~np.isfinite(got)).sum(), bad.sum())
+        if not (net.select and prec == "bf16"):
+            scale = np.max(np.abs(ref[~bad]))
+            assert np.max(np.abs(got[~bad] - ref[~bad])) <= (1e-5 if prec == "fp32" else 2e-2) * scale, label
+    model.close()
+    if other is not model:
+        other.close()
