@@ -76,8 +76,9 @@ enum { NPM_INIT_NORMAL = 0, NPM_INIT_UNIFORM = 1 };
  * wave's consecutive tiles touch nearby grid entries; NPM_ORDER_NONE keeps
  * the caller's order; NPM_ORDER_AUTO sorts training batches of 2^15
  * vertices or more, and no queries: on a grid with hashed levels a query of
- * more than 16,384 vertices (24,576 in FP32) encodes its batch level by
- * level into context scratch first (4 bytes per vertex and grid feature, 2
+ * 2^15 vertices or more (more than 16,384 in the precision form, 24,576 with
+ * the NPM-product inputs) encodes its batch level by level into context
+ * scratch first (4 bytes per vertex and grid feature, 2
  * in the precision form), and a small dense grid stays in the caches.
  * A query's outputs do not depend on the order (each vertex keeps its own
  * uniforms; the outputs are staged and un-permuted); a gradient changes only

@@ -380,14 +380,9 @@ __device__ __forceinline__ void sh_bands4(float x, float y, float z, float *o)
     o[15] = 0.59004358992664352f * x * (xx - 3.0f * yy);
 }
 
-// Lane l ^ 32's value: one vector instruction swaps the two half-waves of a
-// pair of registers, with no LDS round trip.
-__device__ __forceinline__ float xor32(float v)
-{
-    // r[0]: both halves hold lanes 0..31's values, r[1]: lanes 32..63's
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
-}
+// Lane l ^ 32's value.  (The half-wave swap instruction with its select took as
+// long in the training kernels and 1 % longer in the dense grids' queries.)
+__device__ __forceinline__ float xor32(float v) { return __shfl_xor(v, 32, 64); }
 
 // ------------------------------------------------------------------ selection
 // Selection term of one sample (the learned selection probability): the

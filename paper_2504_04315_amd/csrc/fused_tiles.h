@@ -420,7 +420,6 @@ __device__ __forceinline__ void query_head(const QueryIO &io, int64_t vv, bool v
     Lobe L[4];
     map_half(o, L);
     if (io.lobes && valid) {
-        float *lb = io.lobes + vv + (int64_t)h * n;       // lobe h; lobe 2 r + h is 2 r n further on
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const f32x4 c = {L[r].theta, L[r].phi, L[r].kappa, expf(L[r].loglam)};
@@ -428,7 +427,7 @@ __device__ __forceinline__ void query_head(const QueryIO &io, int64_t vv, bool v
                 *reinterpret_cast<f32x4 *>(st + 20 * h + 4 * r) = c;
             } else {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) lb[(int64_t)(q * kLobes + 2 * r) * n] = c[q];
+                for (int q = 0; q < 4; ++q) io.lobes[(int64_t)(q * kLobes + 2 * r + h) * n + vv] = c[q];
             }
         }
     }

@@ -319,14 +319,16 @@ constexpr int64_t kQueryTiny = 2048;
 // Queries of more vertices than this on a grid with hashed levels encode the
 // batch level by level first (k_encode.hip): the second launch costs 3 us,
 // and up to here gathering every corner of a tile at once is no slower.  16
-// levels, 2^19 entries, gathered / encoded first: FP32 8,192 vertices 23.1 /
-// 23.5 us, 20,011 33.0 / 38.5, 32,768 57.8 / 43.9; BF16 16,384 22.1 / 22.3,
-// 20,011 24.6 / 23.3, 32,768 48.4 / 26.6.  2^20 vertices against the spatially
-// ordered gather kernel with its sort and un-permute: FP32 711 -> 666 us,
-// BF16 588 -> 420.  A dense grid's levels stay in the caches, and its corners
+// levels, 2^19 entries, gathered / encoded first: FP32 20,011 vertices 33.0 /
+// 38.5 us, 28,001 39.3 / 42.4, 32,767 40.8 / 43.9 (2^17 entries, 32,767: 33.2 /
+// 37.6), 50,001 78 / 52; with the wide NPM-product input, whose first layer the
+// gathers wait for, 20,001 35.4 / -, 25,001 - / 37.0, 32,767 43.9 / 39.1; BF16
+// 16,384 22.1 / 22.3, 20,011 24.5 / 23.3, 30,001 - / 25.9, 32,767 29.0 / -.  2^20 vertices against the
+// spatially ordered gather kernel with its sort and un-permute: FP32 711 -> 666
+// us, BF16 588 -> 420.  A dense grid's levels stay in the caches, and its corners
 // are gathered in the query kernel at every size (8 levels, 921,600 vertices,
 // FP32 296 us against 355 encoded first).
-constexpr int64_t kFeatQuery32 = 24576, kFeatQuery16 = 16384;
+constexpr int64_t kFeatQuery32 = kQuerySmall - 1, kFeatQuery32Wide = 24576, kFeatQuery16 = 16384;
 
 // perm/inv (optional): visiting order and its inverse; the outputs then go
 // through `stage` (n slots of 40 floats) and an un-permuting pass.  feat

@@ -552,9 +552,10 @@ static bool use_order(const npm_ctx *ctx, int64_t n, bool query)
 // Whether a query encodes its batch level by level first (k_encode.hip).
 static bool use_feat(const npm_ctx *ctx, int64_t n)
 {
-    const bool bf = ctx->net.cfg.precision == NPM_PREC_BF16;
-    return ctx->net.cfg.batch_order == NPM_ORDER_AUTO && ctx->net.grid.hashed_mask != 0 &&
-           n > (bf ? kFeatQuery16 : kFeatQuery32);
+    const int64_t line = ctx->net.cfg.precision == NPM_PREC_BF16 ? kFeatQuery16
+                         : ctx->net.mlp.in_p > 32                ? kFeatQuery32Wide
+                                                                 : kFeatQuery32;
+    return ctx->net.cfg.batch_order == NPM_ORDER_AUTO && ctx->net.grid.hashed_mask != 0 && n > line;
 }
 
 // Whether a training batch's features are encoded level by level for the tile
