@@ -78,8 +78,10 @@ enum { NPM_INIT_NORMAL = 0, NPM_INIT_UNIFORM = 1 };
  * vertices or more, and no queries: on a grid with hashed levels a query of
  * 2^15 vertices or more (more than 16,384 in the precision form, 24,576 with
  * the NPM-product inputs) encodes its batch level by level into context
- * scratch first (4 bytes per vertex and grid feature, 2
- * in the precision form), and a small dense grid stays in the caches.
+ * scratch first (4 bytes per vertex and grid feature, 2 in the precision
+ * form; up to 2^15 vertices it is there from npm_create on, and without room
+ * for it, or where it would have to grow under stream capture, the query
+ * gathers instead), and a small dense grid stays in the caches.
  * A query's outputs do not depend on the order (each vertex keeps its own
  * uniforms; the outputs are staged and un-permuted); a gradient changes only
  * in the order of its floating-point sums.                                  */

@@ -108,8 +108,12 @@ struct npm_ctx {
     uint32_t *s_cells = nullptr;       // 2^18 cell counts / offsets, 256 block totals
     int64_t sort_n = 0;
     // per-tile dG of a fused training batch, for the aggregated scatter
-    float *s_dgt = nullptr;            // [dgt_tiles][max(in_p, 32)][32]
-    int64_t dgt_tiles = 0;
+    // ([tiles][max(in_p, 32)][32]), and behind it the batch's grid features
+    // where the tile kernel reads them and there was room (dgt_short: there
+    // was not)
+    float *s_dgt = nullptr;
+    size_t dgt_words = 0;
+    bool dgt_short = false;
     // binned scatter of the hashed levels: per-chunk bin counts / offsets
     // (and the scan's block totals), and the binned items
     uint32_t *s_bin_cnt = nullptr, *s_bin_items = nullptr;
@@ -163,6 +167,10 @@ struct Launch {
 // Timing bracket (no-op unless enabled).
 void timed_begin(npm_ctx *ctx, const char *name, hipStream_t s, int *token);
 void timed_end(npm_ctx *ctx, int token, hipStream_t s);
+
+// npm_create; reserve: with the feature scratch of the queries that are too small
+// to be sorted, so that they never allocate
+npm_status create_context(const npm_config *cfg, bool reserve, npm_ctx **out);
 
 // common kernels (k_common.hip)
 hipError_t launch_init_params(npm_ctx *ctx, hipStream_t s);

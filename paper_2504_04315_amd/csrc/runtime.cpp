@@ -332,7 +332,11 @@ static void free_ctx(npm_ctx *ctx)
     delete ctx;
 }
 
-npm_status npm_create(const npm_config *cfg, npm_ctx **out)
+static bool use_feat(const npm_ctx *ctx, int64_t n);
+
+}  // extern "C"
+
+npm_status npm::create_context(const npm_config *cfg, bool reserve, npm_ctx **out)
 {
     if (!cfg || !out) return fail(NPM_ERR_INVALID_ARG, "null argument");
     *out = nullptr;
@@ -399,8 +403,25 @@ npm_status npm_create(const npm_config *cfg, npm_ctx **out)
         free_ctx(ctx);
         return hip_fail(e, "npm_create");
     }
+    // (without room for it such a query gathers)
+    const int64_t small = kSortMinBatch - 1;
+    if (reserve && net.cfg.exec_mode == NPM_EXEC_FUSED && use_feat(ctx, small)) {
+        if (hipMalloc((void **)&ctx->s_feat, feat_words(net, small) * 4) == hipSuccess) {
+            ctx->feat_cap = feat_words(net, small);
+        } else {
+            ctx->s_feat = nullptr;
+            (void)hipGetLastError();
+        }
+    }
     *out = ctx;
     return NPM_OK;
+}
+
+extern "C" {
+
+npm_status npm_create(const npm_config *cfg, npm_ctx **out)
+{
+    return create_context(cfg, true, out);
 }
 
 npm_status npm_destroy(npm_ctx *ctx)
@@ -458,8 +479,7 @@ static npm_status check_aux(npm_ctx *ctx, int64_t n, const float *aux)
 static bool use_order(const npm_ctx *ctx, int64_t n, bool query = false);
 static hipError_t ensure_sort(npm_ctx *ctx, int64_t n);
 static hipError_t ensure_qstage(npm_ctx *ctx, int64_t n);
-static bool use_feat(const npm_ctx *ctx, int64_t n);
-static hipError_t ensure_feat(npm_ctx *ctx, int64_t n);
+static hipError_t ensure_feat(npm_ctx *ctx, int64_t n, hipStream_t s, bool *have);
 
 npm_status npm_query(npm_ctx *ctx, int64_t n, const float *pos, const float *dir,
                      uint64_t rng_seed, uint32_t rng_stream, float *lobes, float *pdf,
@@ -482,8 +502,9 @@ static npm_status query_impl(npm_ctx *ctx, int64_t n, const float *pos, const fl
             const uint32_t *perm = nullptr;
             void *feat = nullptr;
             if (use_feat(ctx, n) && any) {
-                NPM_HIP(ensure_feat(ctx, n), "feature scratch allocation");
-                feat = ctx->s_feat;
+                bool have;      // without room the corners are gathered in the query kernel
+                NPM_HIP(ensure_feat(ctx, n, s, &have), "feature scratch allocation");
+                feat = have ? ctx->s_feat : nullptr;
             } else if (use_order(ctx, n, true) && any) {
                 NPM_HIP(ensure_sort(ctx, n), "order scratch allocation");
                 NPM_HIP(ensure_qstage(ctx, n), "query staging allocation");
@@ -562,19 +583,44 @@ static bool use_feat(const npm_ctx *ctx, int64_t n)
 // kernel of k_train.hip.
 static bool train_feat(const npm_ctx *ctx) { return train_tile_takes(ctx->net); }
 
-static hipError_t ensure_feat(npm_ctx *ctx, int64_t n)
+// Whether scratch may not grow now: `s` is being captured, or another stream is
+// in a way that concerns it (the null stream).
+static bool capturing(hipStream_t s)
 {
-    const size_t words = feat_words(ctx->net, n);
-    if (words <= ctx->feat_cap) return hipSuccess;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+// Grows *p to `words` 32-bit words after the device has finished with it; without
+// room it is left empty and the call succeeds.
+static hipError_t grow_words(void **p, size_t *cap, size_t words)
+{
     hipError_t e = hipDeviceSynchronize();
     if (e != hipSuccess) return e;
-    if (ctx->s_feat) (void)hipFree(ctx->s_feat);
-    ctx->s_feat = nullptr;
-    ctx->feat_cap = 0;
-    e = hipMalloc((void **)&ctx->s_feat, words * 4);
-    if (e != hipSuccess) return e;
-    ctx->feat_cap = words;
-    return hipSuccess;
+    if (*p) (void)hipFree(*p);
+    *p = nullptr;
+    *cap = 0;
+    e = hipMalloc(p, words * 4);
+    if (e == hipSuccess) {
+        *cap = words;
+        return hipSuccess;
+    }
+    *p = nullptr;
+    (void)hipGetLastError();
+    return e == hipErrorOutOfMemory ? hipSuccess : e;
+}
+
+// *have: the feature scratch holds n vertices (it does not where the device has
+// no room, or where it would have to grow under capture)
+static hipError_t ensure_feat(npm_ctx *ctx, int64_t n, hipStream_t s, bool *have)
+{
+    const size_t words = feat_words(ctx->net, n);
+    hipError_t e = hipSuccess;
+    if (words > ctx->feat_cap && !capturing(s)) e = grow_words((void **)&ctx->s_feat, &ctx->feat_cap, words);
+    *have = words <= ctx->feat_cap;
+    return e;
 }
 
 // The binned pass of a fused training batch: the plan, or false for the
@@ -589,27 +635,18 @@ static bool use_bins(const npm_ctx *ctx, int64_t n, bool ordered, BinDesc *b)
     return mode == NPM_SCATTER_BINNED || b->nbins >= kBinMinBins;
 }
 
-static hipError_t ensure_bins(npm_ctx *ctx, const BinDesc &b)
+// *have: the bins' buffers hold the plan (as for ensure_feat)
+static hipError_t ensure_bins(npm_ctx *ctx, const BinDesc &b, hipStream_t s, bool *have)
 {
     const size_t cw = bin_count_words(b), iw = bin_item_words(b, ctx->net.grid.feat);
-    if (cw <= ctx->bin_cnt_words && iw <= ctx->bin_item_words) return hipSuccess;
-    hipError_t e = hipDeviceSynchronize();
-    if (e != hipSuccess) return e;
-    if (cw > ctx->bin_cnt_words) {
-        if (ctx->s_bin_cnt) (void)hipFree(ctx->s_bin_cnt);
-        ctx->s_bin_cnt = nullptr;
-        ctx->bin_cnt_words = 0;
-        if ((e = hipMalloc((void **)&ctx->s_bin_cnt, cw * 4)) != hipSuccess) return e;
-        ctx->bin_cnt_words = cw;
+    hipError_t e = hipSuccess;
+    if ((cw > ctx->bin_cnt_words || iw > ctx->bin_item_words) && !capturing(s)) {
+        if (cw > ctx->bin_cnt_words) e = grow_words((void **)&ctx->s_bin_cnt, &ctx->bin_cnt_words, cw);
+        if (e == hipSuccess && iw > ctx->bin_item_words)
+            e = grow_words((void **)&ctx->s_bin_items, &ctx->bin_item_words, iw);
     }
-    if (iw > ctx->bin_item_words) {
-        if (ctx->s_bin_items) (void)hipFree(ctx->s_bin_items);
-        ctx->s_bin_items = nullptr;
-        ctx->bin_item_words = 0;
-        if ((e = hipMalloc((void **)&ctx->s_bin_items, iw * 4)) != hipSuccess) return e;
-        ctx->bin_item_words = iw;
-    }
-    return hipSuccess;
+    *have = cw <= ctx->bin_cnt_words && iw <= ctx->bin_item_words;
+    return e;
 }
 
 static hipError_t ensure_qstage(npm_ctx *ctx, int64_t n)
@@ -650,26 +687,21 @@ static hipError_t ensure_sort(npm_ctx *ctx, int64_t n)
 
 // The per-tile dG of a training batch and, behind it, the batch's features
 // where the tile kernel reads them (train_feat): one allocation, which the
-// first step of a size waits for.
-static float *train_features(npm_ctx *ctx)
+// first step of a size waits for.  Where the device has room for the dG alone
+// *feat is null, and the gathering kernel trains the batch.
+static hipError_t ensure_dgt(npm_ctx *ctx, int64_t n, float **feat)
 {
-    return ctx->s_dgt + ctx->dgt_tiles * (int64_t)std::max(ctx->net.mlp.in_p, 32) * 32;
-}
-
-static hipError_t ensure_dgt(npm_ctx *ctx, int64_t n)
-{
-    const int64_t tiles = (n + 31) / 32;
-    if (tiles <= ctx->dgt_tiles) return hipSuccess;
-    hipError_t e = hipDeviceSynchronize();
-    if (e != hipSuccess) return e;
-    if (ctx->s_dgt) (void)hipFree(ctx->s_dgt);
-    ctx->s_dgt = nullptr;
-    ctx->dgt_tiles = 0;
-    const int64_t rows = std::max(ctx->net.mlp.in_p, 32);
-    const size_t feat = train_feat(ctx) ? feat_words(ctx->net, tiles * 32) : 0;
-    e = hipMalloc((void **)&ctx->s_dgt, ((size_t)tiles * rows * 32 + feat) * sizeof(float));
-    if (e != hipSuccess) return e;
-    ctx->dgt_tiles = tiles;
+    const size_t tiles = (size_t)((n + 31) / 32);
+    const size_t dg = tiles * (size_t)std::max(ctx->net.mlp.in_p, 32) * 32;
+    const size_t all = dg + (train_feat(ctx) ? feat_words(ctx->net, (int64_t)tiles * 32) : 0);
+    if (ctx->dgt_words < dg || (ctx->dgt_words < all && !ctx->dgt_short)) {
+        hipError_t e = grow_words((void **)&ctx->s_dgt, &ctx->dgt_words, all);
+        ctx->dgt_short = e == hipSuccess && !ctx->s_dgt && dg < all;
+        if (ctx->dgt_short) e = grow_words((void **)&ctx->s_dgt, &ctx->dgt_words, dg);
+        if (e == hipSuccess && !ctx->s_dgt) e = hipErrorOutOfMemory;
+        if (e != hipSuccess) return e;
+    }
+    *feat = all > dg && ctx->dgt_words >= all ? ctx->s_dgt + dg : nullptr;
     return hipSuccess;
 }
 
@@ -682,17 +714,18 @@ static npm_status backward_impl(npm_ctx *ctx, int64_t n, const float *pos, const
         const uint32_t *perm = nullptr;
         const bool ordered = grad && use_order(ctx, n);
         BinDesc bins;
-        const bool binned = grad && use_bins(ctx, n, ordered, &bins);
+        bool binned = grad && use_bins(ctx, n, ordered, &bins);
+        float *feat = nullptr;
         if (ordered) NPM_HIP(ensure_sort(ctx, n), "order scratch allocation");
-        if (grad) NPM_HIP(ensure_dgt(ctx, n), "dG scratch allocation");
-        if (binned) NPM_HIP(ensure_bins(ctx, bins), "bin scratch allocation");
+        if (grad) NPM_HIP(ensure_dgt(ctx, n, &feat), "dG scratch allocation");
+        // without room for the bins every level takes the chunked scatter
+        if (binned) NPM_HIP(ensure_bins(ctx, bins, s, &binned), "bin scratch allocation");
         if (ordered) {
             NPM_HIP(spatial_order(ctx, n, pos, aux, dir, rad, spdf, ctx->s_perm, ctx->s_inv,
                                   ctx->s_rec, ctx->s_cells, s, binned ? ctx->s_bin_cnt : nullptr,
                                   binned ? bin_clear_words(bins) : 0), "spatial order");
             perm = ctx->s_perm;
         }
-        void *feat = grad && train_feat(ctx) ? train_features(ctx) : nullptr;
         NPM_HIP(fused_backward(ctx, n, pos, aux, dir, rad, spdf, grad, loss_out, perm,
                                perm ? ctx->s_rec : nullptr, grad ? ctx->s_dgt : nullptr,
                                binned ? &bins : nullptr, s, bsdf, feat),

@@ -359,7 +359,7 @@ npm_status npm_session_create(npm_server *s, const npm_config *cfg, int32_t *sid
     s->sessions[slot].reserved = true;
     lk.unlock();
     npm_ctx *ctx = nullptr;
-    st = npm_create(&c, &ctx);
+    st = create_context(&c, !shared, &ctx);     // the shared kernels query without scratch
     lk.lock();
     Session &se = s->sessions[slot];
     se.reserved = false;
