@@ -26,10 +26,13 @@
  * All request buffers are caller-owned DEVICE pointers in the layouts of
  * npm_query / npm_backward, and must stay valid until npm_wait returns for
  * the request.  A round's training batches use scratch of the server's own
- * beside the budget (128 bytes per vertex, and 16 (2 + F) bytes per vertex and
- * hashed level of the largest batch that is binned), which grows to the largest
- * round and goes with the server; without room for it a round still runs, its
- * grid scatter slower.  Every call returns an npm_status and sets npm_last_error().
+ * (128 bytes per vertex, and 16 (2 + F) bytes per vertex and hashed level of
+ * the largest batch that is binned).  It is sized for round_vertices when a
+ * session is created, out of what the resident sessions leave of the budget,
+ * and shrinks when a session needs the room: it never keeps a session out, and
+ * sessions and scratch stay within the budget.  A batch that finds no room in
+ * it still trains, its grid scatter slower.
+ * Every call returns an npm_status and sets npm_last_error().
  */
 #ifndef NPM_SERVE_H
 #define NPM_SERVE_H
@@ -43,7 +46,8 @@ extern "C" {
 typedef struct npm_server npm_server;
 
 typedef struct {
-    int64_t budget_bytes;    /* HBM budget for resident sessions (> 0)           */
+    int64_t budget_bytes;    /* HBM budget of the resident sessions, and of the
+                                rounds' scratch in what they leave (> 0)         */
     int32_t max_sessions;    /* session slots, 1..256                            */
     int32_t round_vertices;  /* vertex capacity of one round (>= 1024)           */
     int32_t plain_path;      /* 1: run every request through its session's own

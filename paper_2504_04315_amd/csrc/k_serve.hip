@@ -127,9 +127,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // Scattered from here, 16 levels of 36,868 unordered vertices took 2.4 M line
 // requests of memory-side atomics from 73 blocks: 263 us, now 74 with two
 // rounds of tiles a chunk, so that every CU has a block, and 100 for the
-// scatters.  Only where the device has no room for the dG does a tile scatter
-// from the wave's LDS buffer, its coarse levels through a 32-bit fixed-point
-// window, the rest by FP32 atomics.
+// scatters.  A request whose dG found no room in the server's scratch is scattered
+// tile by tile from the wave's LDS buffer, its coarse levels through a 32-bit
+// fixed-point window, the rest by FP32 atomics.
 template <int IN_P, int HID_P, int NH, int F>
 __global__ __launch_bounds__(256) void k_serve_train(RoundHdr *hdr, const DevReq *__restrict__ reqs,
                                                      int r0, int r1, int n_chunks, int which,
@@ -314,26 +314,60 @@ void serve_lanes_free(ServeLanes *l)
     *l = ServeLanes{};
 }
 
-// Grows b to `words` 32-bit words.  The rounds before this one may still use
-// it: their stream is drained first (and it has waited for the side stream).
-// False, with b empty, where the device has no room.  The scheduler's thread
-// allocates whatever another thread's streams are capturing.
-static bool grow(ServeBuf *b, size_t words, hipStream_t s)
+// The binned levels of a training batch of n vertices (in its own order) on
+// ctx's grid, or false.
+static bool request_bins(const npm_ctx *ctx, int64_t n, BinDesc *b)
 {
-    if (words <= b->words) return true;
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
-    bool ok = hipStreamSynchronize(s) == hipSuccess;
-    if (ok) {
-        if (b->p) (void)hipFree(b->p);
-        b->p = nullptr;
-        b->words = 0;
-        ok = hipMalloc((void **)&b->p, words * 4) == hipSuccess;
-        if (ok) b->words = words;
-        else (void)hipGetLastError();
+    const int mode = ctx->net.cfg.scatter_mode;
+    return mode != NPM_SCATTER_ATOMIC && (mode == NPM_SCATTER_BINNED || n >= kBinMinBatch) &&
+           bin_plan(ctx, n, false, b) && (mode == NPM_SCATTER_BINNED || b->nbins >= kBinMinBins);
+}
+
+static size_t dgt_words(int64_t n) { return (size_t)((n + 31) / 32) * kServeRows * 32; }
+
+void serve_lanes_size(ServeLanes *l, int64_t vertices, int64_t bytes,
+                      const std::vector<const npm_ctx *> &nets, hipStream_t s)
+{
+    ServeBuf *const bufs[3] = {&l->dgt, &l->cnt, &l->items};
+    bool drained = false;
+    if (nets.empty()) vertices = bytes = 0;       // nothing to scatter: given back
+    bytes = std::max<int64_t>(bytes, 0);
+    for (;; vertices /= 2) {
+        size_t want[3] = {0, 0, 0};
+        if (vertices >= kMinLaneVertices) {
+            // every request of a round may end in a part of a tile
+            want[0] = dgt_words(vertices + 32 * kMaxRoundRequests);
+            for (const npm_ctx *c : nets) {
+                BinDesc b;
+                if (!request_bins(c, vertices, &b)) continue;
+                want[1] = std::max(want[1], bin_count_words(b));
+                want[2] = std::max(want[2], bin_item_words(b, c->net.grid.feat));
+            }
+        }
+        if ((int64_t)(want[0] + want[1] + want[2]) * 4 > bytes) continue;
+        // what is there stays unless it is too small, or more than `bytes`
+        bool fits = true, over = (int64_t)(l->dgt.words + l->cnt.words + l->items.words) * 4 > bytes;
+        for (int i = 0; i < 3; ++i) fits = fits && bufs[i]->words >= want[i];
+        if (fits && !over) return;
+        if (!drained && hipStreamSynchronize(s) != hipSuccess) return;
+        drained = true;
+        bool ok = true;
+        for (int i = 0; i < 3; ++i) {
+            if (bufs[i]->p) (void)hipFree(bufs[i]->p);
+            *bufs[i] = ServeBuf{};
+        }
+        for (int i = 0; i < 3 && ok; ++i) {
+            if (want[i] == 0) continue;
+            ok = hipMalloc((void **)&bufs[i]->p, want[i] * 4) == hipSuccess;
+            if (ok) {
+                bufs[i]->words = want[i];
+            } else {
+                bufs[i]->p = nullptr;
+                (void)hipGetLastError();
+            }
+        }
+        if (ok || vertices == 0) return;
     }
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    return ok;
 }
 
 static int shape_key(const Net &net)
@@ -403,14 +437,6 @@ static int train_chunk_tiles(int64_t tiles)
     return kTrainWaves * (int)std::max<int64_t>(1, std::min<int64_t>(4, rounds));
 }
 
-// The binned levels of a training request (in its own order), or false.
-static bool request_bins(const ServeRequest &q, BinDesc *b)
-{
-    const int mode = q.ctx->net.cfg.scatter_mode;
-    return mode != NPM_SCATTER_ATOMIC && (mode == NPM_SCATTER_BINNED || q.n >= kBinMinBatch) &&
-           bin_plan(q.ctx, q.n, false, b) && (mode == NPM_SCATTER_BINNED || b->nbins >= kBinMinBins);
-}
-
 // The grid scatter of one request's dG (in the request's order: its bins hold
 // every hashed level).
 static hipError_t scatter_request(const ServeRequest &q, ServeLanes *l, const float *dgt,
@@ -418,7 +444,7 @@ static hipError_t scatter_request(const ServeRequest &q, ServeLanes *l, const fl
 {
     const GridDesc &g = q.ctx->net.grid;
     BinDesc b;
-    const bool binned = request_bins(q, &b) && l->cnt.words >= bin_count_words(b) &&
+    const bool binned = request_bins(q.ctx, q.n, &b) && l->cnt.words >= bin_count_words(b) &&
                         l->items.words >= bin_item_words(b, g.feat);
     uint32_t left = g.n_levels >= 32 ? ~0u : (1u << g.n_levels) - 1u;
     if (binned)
@@ -461,26 +487,14 @@ hipError_t serve_launch_round(RoundBuffers *b, ServeLanes *lanes,
     double **hstats = (double **)(host + L.stats);
     DevReq *dr = (DevReq *)(dev + L.reqs);
     double *dloss = (double *)(dev + L.loss);
-    struct Group { int key, kind, r0, r1, chunks, img, tiles; };
+    struct Group { int key, kind, r0, r1, chunks, img, tiles; bool tile_scatter; };
     std::vector<Group> groups;
-    // dG of the round's training batches, one after the other, and the bins of
-    // one batch at a time
-    size_t dgt_words = 0, cnt_words = 0, item_words = 0;
     int64_t train_tiles = 0;
-    for (const ServeRequest &q : in) {
-        if (q.kind == 0) continue;
-        const int64_t tiles = (q.n + 31) / 32;
-        train_tiles += tiles;
-        dgt_words += (size_t)tiles * kServeRows * 32;
-        BinDesc bd;
-        if (request_bins(q, &bd)) {
-            cnt_words = std::max(cnt_words, bin_count_words(bd));
-            item_words = std::max(item_words, bin_item_words(bd, q.ctx->net.grid.feat));
-        }
-    }
+    for (const ServeRequest &q : in)
+        if (q.kind == 1) train_tiles += (q.n + 31) / 32;
     const int per_train = train_chunk_tiles(train_tiles);
-    const bool dgt = grow(&lanes->dgt, dgt_words, s);
-    if (dgt && grow(&lanes->cnt, cnt_words, s)) (void)grow(&lanes->items, item_words, s);
+    // dG of the round's training batches, one after the other, as far as they
+    // fit; the bins hold one batch at a time
     size_t dgt_at = 0;
     for (int j = 0; j < nreq; ++j) {
         const ServeRequest &q = in[order[j]];
@@ -488,7 +502,7 @@ hipError_t serve_launch_round(RoundBuffers *b, ServeLanes *lanes,
         const Net &net = ctx->net;
         const int key = shape_key(net);
         if (groups.empty() || groups.back().key != key || groups.back().kind != q.kind)
-            groups.push_back({key, q.kind, j, j, 0, 0, q.kind == 0 ? kQueryChunkTiles : per_train});
+            groups.push_back({key, q.kind, j, j, 0, 0, q.kind == 0 ? kQueryChunkTiles : per_train, false});
         Group &g = groups.back();
         DevReq &d = hr[j];
         std::memset(&d, 0, sizeof(d));
@@ -511,9 +525,13 @@ hipError_t serve_launch_round(RoundBuffers *b, ServeLanes *lanes,
         d.width = net.mlp.width;
         d.invN = q.n > 0 ? 1.0f / (float)q.n : 0.0f;
         const int64_t tiles = (q.n + 31) / 32;
-        if (q.kind == 1 && dgt) {
-            d.dgt = (float *)lanes->dgt.p + dgt_at;
-            dgt_at += (size_t)tiles * kServeRows * 32;
+        if (q.kind == 1 && q.n > 0) {
+            if (dgt_at + dgt_words(q.n) <= lanes->dgt.words) {
+                d.dgt = (float *)lanes->dgt.p + dgt_at;
+                dgt_at += dgt_words(q.n);
+            } else {
+                g.tile_scatter = true;
+            }
         }
         d.chunk_begin = g.chunks;
         g.chunks += (int)((tiles + g.tiles - 1) / g.tiles);
@@ -543,8 +561,8 @@ hipError_t serve_launch_round(RoundBuffers *b, ServeLanes *lanes,
         for (int gi = 0; gi < (int)groups.size() && e == hipSuccess; ++gi) {
             const Group &g = groups[gi];
             if (g.kind != kind) continue;
-            e = launch_shape(g.key, dh, dr, g.r0, g.r1, g.chunks, gi, kind == 1, g.tiles, !dgt,
-                             g.img, kind == 0 ? sq : s);
+            e = launch_shape(g.key, dh, dr, g.r0, g.r1, g.chunks, gi, kind == 1, g.tiles,
+                             g.tile_scatter, g.img, kind == 0 ? sq : s);
         }
     for (int gi = 0; gi < (int)groups.size() && e == hipSuccess; ++gi) {
         const Group &g = groups[gi];
@@ -552,8 +570,8 @@ hipError_t serve_launch_round(RoundBuffers *b, ServeLanes *lanes,
         hipLaunchKernelGGL(k_serve_finish, dim3((g.r1 - g.r0 + 63) / 64), dim3(64), 0, s, dr,
                            (const double *const *)(dev + L.stats), g.r0, g.r1);
         e = hipGetLastError();
-        for (int j = g.r0; j < g.r1 && dgt && e == hipSuccess; ++j)
-            e = scatter_request(in[order[j]], lanes, hr[j].dgt, s);
+        for (int j = g.r0; j < g.r1 && e == hipSuccess; ++j)
+            if (hr[j].dgt) e = scatter_request(in[order[j]], lanes, hr[j].dgt, s);
     }
     // joined whatever failed: what follows on s, and the round's end, come
     // after the queries too

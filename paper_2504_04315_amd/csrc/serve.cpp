@@ -86,7 +86,8 @@ struct npm_server {
     std::condition_variable cv_inflight;
     bool slot_busy[kSlots] = {false, false, false, false};
     RoundBuffers bufs[kSlots];
-    ServeLanes lanes;             // the scheduler thread's
+    std::mutex lanes_mu;          // taken before mu where both are
+    ServeLanes lanes;             // used by the round being launched, sized by create_session
     uint64_t next_id = 1;
     int64_t next_round = 0;
     int64_t bytes_in_use = 0;
@@ -146,7 +147,7 @@ hipError_t execute_plain(const std::vector<ServeRequest> &work, hipStream_t stre
 
 void scheduler(npm_server *s)
 {
-    (void)hipSetDevice(s->device);    // the lanes' scratch belongs to the sessions' device
+    (void)hipSetDevice(s->device);
     std::unique_lock<std::mutex> lk(s->mu);
     for (;;) {
         s->cv_sched.wait(lk, [&] { return s->stop || (!s->pending.empty() && !s->held); });
@@ -191,9 +192,13 @@ void scheduler(npm_server *s)
             work.push_back(w);
         }
         lk.unlock();
-        const hipError_t e = plain ? execute_plain(work, s->stream)
-                                   : serve_launch_round(&s->bufs[slot], &s->lanes, work,
-                                                        s->stream);
+        hipError_t e;
+        if (plain) {
+            e = execute_plain(work, s->stream);
+        } else {
+            std::lock_guard<std::mutex> ll(s->lanes_mu);
+            e = serve_launch_round(&s->bufs[slot], &s->lanes, work, s->stream);
+        }
         // The event follows whatever part of the round did launch (also when
         // a later launch failed): the completion thread releases the round's
         // descriptor buffer only after the device has passed it.  Without an
@@ -247,6 +252,22 @@ void completer(npm_server *s)
         s->cv_slot.notify_all();
         s->cv_done.notify_all();
     }
+}
+
+// Sizes the rounds' training scratch for the resident shared sessions, within
+// what they leave of the budget: a session that needs the room gets it back.
+void size_lanes(npm_server *s)
+{
+    std::lock_guard<std::mutex> ll(s->lanes_mu);
+    std::vector<const npm_ctx *> nets;
+    int64_t left;
+    {
+        std::lock_guard<std::mutex> lk(s->mu);
+        left = s->cfg.budget_bytes - s->bytes_in_use;
+        for (const Session &se : s->sessions)
+            if (se.alive && se.shared) nets.push_back(se.ctx);
+    }
+    serve_lanes_size(&s->lanes, s->cfg.round_vertices, left, nets, s->stream);
 }
 
 }  // namespace
@@ -358,6 +379,7 @@ npm_status npm_session_create(npm_server *s, const npm_config *cfg, int32_t *sid
     s->bytes_in_use += bytes;
     s->sessions[slot].reserved = true;
     lk.unlock();
+    size_lanes(s);                              // room for the session, if the scratch has it
     npm_ctx *ctx = nullptr;
     st = create_context(&c, !shared, &ctx);     // the shared kernels query without scratch
     lk.lock();
@@ -374,6 +396,8 @@ npm_status npm_session_create(npm_server *s, const npm_config *cfg, int32_t *sid
     se.outstanding = 0;
     s->stats.sessions += 1;
     *sid = slot;
+    lk.unlock();
+    if (shared) size_lanes(s);
     return NPM_OK;
 }
 
@@ -392,7 +416,9 @@ npm_status npm_session_destroy(npm_server *s, int32_t sid)
     s->stats.sessions -= 1;
     lk.unlock();
     (void)hipStreamSynchronize(s->stream);   // npm_destroy synchronises the device as well
-    return npm_destroy(ctx);
+    const npm_status st = npm_destroy(ctx);
+    size_lanes(s);                           // the last shared session's scratch goes with it
+    return st;
 }
 
 npm_status npm_session_ctx(npm_server *s, int32_t sid, npm_ctx **ctx)

@@ -33,8 +33,9 @@ struct RoundBuffers {
 // The server's second stream (default priority) for rounds of both kinds, and
 // the training scratch of a round: the per-tile dG of its batches and the bins
 // of one of them.  The rounds of a server run one after the other on its
-// stream, so one set serves them all; it grows to the largest round and goes
-// with the server.
+// stream, so one set serves them all.  It is sized when a session is created
+// and not by the rounds: growing under traffic stalled them (a first load of 32
+// sessions' 224 requests 800 -> 650 M vertices/s).
 struct ServeBuf {
     uint32_t *p = nullptr;
     size_t words = 0;
@@ -47,6 +48,13 @@ struct ServeLanes {
 
 hipError_t serve_lanes_init(ServeLanes *l);
 void serve_lanes_free(ServeLanes *l);
+// Sizes the scratch for rounds of `vertices` training vertices of the sessions
+// `nets`, or of the largest power-of-two part of them that `bytes` hold (none
+// below kMinLaneVertices).  `s`, the rounds' stream, is drained before anything
+// is freed.  A device without room leaves it smaller, down to nothing.
+constexpr int64_t kMinLaneVertices = 2048;
+void serve_lanes_size(ServeLanes *l, int64_t vertices, int64_t bytes,
+                      const std::vector<const npm_ctx *> &nets, hipStream_t s);
 hipError_t round_buffers_init(RoundBuffers *b);
 void round_buffers_free(RoundBuffers *b);
 // Whether the persistent kernels are instantiated for this network shape.

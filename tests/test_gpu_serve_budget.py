@@ -1,0 +1,84 @@
+"""The rounds' training scratch of a server: it is there before the first round, so
+that no round allocates; it stays within what the sessions leave of the budget
+and never keeps a session out; and a batch that finds no room in it, or none
+for its bins, takes the slower scatters with the same result.  Each batch's
+first Adam moment equals the session's own fused step up to the order of FP32
+sums (1e-5 of the oracle's condition scale, the FP32 tolerance)."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+import parity as P
+from paper_2504_04315_amd import npm as B
+from paper_2504_04315_amd import serve as S
+from paper_2504_04315_amd import workload as W
+from test_gpu_serve import dev, oracle_net
+
+pytestmark = pytest.mark.gpu
+
+
+def _args(torch, n, seed):
+    b = W.make_batch("surface", n, seed=seed)
+    return b, [dev(torch, a) for a in (b.pos, b.dir, b.radiance, b.pdf)]
+
+
+def test_rounds_allocate_nothing():
+    import torch
+    srv = S.Server(budget_bytes=8 << 30, max_sessions=4, round_vertices=1 << 18)
+    sids = [srv.create_session(B.make_config(replace(W.CFG5, seed=70 + k))) for k in range(2)]
+    jobs = [_args(torch, n, 71 + k)[1] for k, n in enumerate((513, 20001, 60001, 150001))]
+    srv.wait(srv.submit_train(sids[0], *_args(torch, 20011, 70)[1]))  # loads the code
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    for a in jobs:
+        srv.hold(True)
+        for sid in sids:
+            srv.submit_train(sid, *a)
+        srv.drain()
+    torch.cuda.synchronize()
+    # (the runtime's own few megabytes aside; these rounds' scratch is 300)
+    assert free - torch.cuda.mem_get_info()[0] <= 8 << 20
+    srv.close()
+
+
+@pytest.mark.parametrize("extra", [0, 2 << 20, 24 << 20, 400 << 20])
+def test_training_within_the_budget(O, extra):
+    import torch
+    kinds = [(W.CFG5, B.SCATTER_AUTO, 513), (replace(W.CFG5, seed=81), B.SCATTER_AUTO, 20011),
+             (replace(W.CFG5, seed=82), B.SCATTER_BINNED, 17001), (replace(W.PAPER, precision="bf16"),
+                                                                   B.SCATTER_AUTO, 3001)]
+    cfgs = [B.make_config(net, scatter_mode=mode) for net, mode, _ in kinds]
+    need = sum(B.layout_of(c).device_bytes for c in cfgs)
+    srv = S.Server(budget_bytes=int(need + extra), max_sessions=8, round_vertices=1 << 16)
+    sids = [srv.create_session(c) for c in cfgs]            # the scratch keeps none out
+    assert srv.stats().bytes_in_use == need
+    if extra < 1 << 30:
+        with pytest.raises(B.NPMError, match="NPM_ERR_BUDGET"):
+            for _ in range(5):
+                srv.create_session(cfgs[0] if extra < 100 << 20 else B.make_config(W.CFG3))
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    srv.hold(True)
+    jobs = []
+    for (net, _, n), sid in zip(kinds, sids):
+        b, args = _args(torch, n, 90 + n % 7)
+        jobs.append((net, b, args))
+        srv.submit_train(sid, *args)
+    srv.drain()
+    for (net, b, args), cfg, sid in zip(jobs, cfgs, sids):
+        own = B.NPM(cfg)
+        p0 = own.get_state().astype(np.float64)
+        own.train_step(*args)
+        torch.cuda.synchronize()
+        m_own = own.get_state(B.STATE_ADAM_M).astype(np.float64)
+        m_srv = srv.session_state(sid, own.n_params, B.STATE_ADAM_M).astype(np.float64)
+        cond = O.backward_cond(oracle_net(O, net), b.pos, b.dir, b.radiance, b.pdf, p0)
+        c1 = float(1.0 - np.float32(net.beta1))
+        print(P.assert_within(f"extra={extra >> 20} MB n={b.n}", m_srv, m_own,
+                              c1 * 1e-5 * cond + 1e-30), flush=True)
+        own.close()
+    for sid in sids:
+        srv.destroy_session(sid)
+    srv.close()
+    assert torch.cuda.mem_get_info()[0] - free >= need      # the scratch went with the sessions
