@@ -493,9 +493,9 @@ __global__ __launch_bounds__(kBinReduceThreads) void k_bin_reduce(GridDesc g, Bi
 // Which levels are binned, and the sizes of the pass: every hashed level of
 // an unordered batch; of a spatially ordered one, the hashed levels with
 // D_l >= kBinMinResOrdered (coarser ones share lines within a chunk).
-bool bin_plan(const npm_ctx *ctx, int64_t n, bool ordered, BinDesc *out)
+bool bin_plan(const Net &net, int64_t n, bool ordered, BinDesc *out)
 {
-    const GridDesc &g = ctx->net.grid;
+    const GridDesc &g = net.grid;
     const int F = g.feat;
     if (n <= 0 || !g.hashed_mask || (F != 1 && F != 2 && F != 4)) return false;
     BinDesc b{};

@@ -323,19 +323,19 @@ void serve_lanes_free(ServeLanes *l)
     *l = ServeLanes{};
 }
 
-// The binned levels of a training batch of n vertices (in its own order) on
-// ctx's grid, or false.
-static bool request_bins(const npm_ctx *ctx, int64_t n, BinDesc *b)
+// The binned levels of a training batch of n vertices (in its own order) of the
+// network, or false.
+static bool request_bins(const Net &net, int64_t n, BinDesc *b)
 {
-    const int mode = ctx->net.cfg.scatter_mode;
+    const int mode = net.cfg.scatter_mode;
     return mode != NPM_SCATTER_ATOMIC && (mode == NPM_SCATTER_BINNED || n >= kBinMinBatch) &&
-           bin_plan(ctx, n, false, b) && (mode == NPM_SCATTER_BINNED || b->nbins >= kBinMinBins);
+           bin_plan(net, n, false, b) && (mode == NPM_SCATTER_BINNED || b->nbins >= kBinMinBins);
 }
 
 static size_t dgt_words(int64_t n) { return (size_t)((n + 31) / 32) * kServeRows * 32; }
 
 void serve_lanes_size(ServeLanes *l, int64_t vertices, int64_t bytes,
-                      const std::vector<const npm_ctx *> &nets, hipStream_t s)
+                      const std::vector<Net> &nets, hipStream_t s)
 {
     ServeBuf *const bufs[3] = {&l->dgt, &l->cnt, &l->items};
     bool drained = false;
@@ -346,11 +346,11 @@ void serve_lanes_size(ServeLanes *l, int64_t vertices, int64_t bytes,
         if (vertices >= kMinLaneVertices) {
             // every request of a round may end in a part of a tile
             want[0] = dgt_words(vertices + 32 * kMaxRoundRequests);
-            for (const npm_ctx *c : nets) {
+            for (const Net &net : nets) {
                 BinDesc b;
-                if (!request_bins(c, vertices, &b)) continue;
+                if (!request_bins(net, vertices, &b)) continue;
                 want[1] = std::max(want[1], bin_count_words(b));
-                want[2] = std::max(want[2], bin_item_words(b, c->net.grid.feat));
+                want[2] = std::max(want[2], bin_item_words(b, net.grid.feat));
             }
         }
         if ((int64_t)(want[0] + want[1] + want[2]) * 4 > bytes) continue;
@@ -453,7 +453,7 @@ static hipError_t scatter_request(const ServeRequest &q, ServeLanes *l, const fl
 {
     const GridDesc &g = q.ctx->net.grid;
     BinDesc b;
-    const bool binned = request_bins(q.ctx, q.n, &b) && l->cnt.words >= bin_count_words(b) &&
+    const bool binned = request_bins(q.ctx->net, q.n, &b) && l->cnt.words >= bin_count_words(b) &&
                         l->items.words >= bin_item_words(b, g.feat);
     uint32_t left = g.n_levels >= 32 ? ~0u : (1u << g.n_levels) - 1u;
     if (binned)

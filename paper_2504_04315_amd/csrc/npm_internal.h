@@ -277,7 +277,7 @@ struct BinDesc {
     int64_t cap;                       // item (corner pair) capacity: n * 4 * nb
 };
 // false when the batch has no level to bin or exceeds the pass's limits
-bool bin_plan(const npm_ctx *ctx, int64_t n, bool ordered, BinDesc *out);
+bool bin_plan(const Net &net, int64_t n, bool ordered, BinDesc *out);
 size_t bin_count_words(const BinDesc &b);
 int bin_clear_words(const BinDesc &b);     // the first words of the counters
 size_t bin_item_words(const BinDesc &b, int feat);

@@ -256,18 +256,26 @@ void completer(npm_server *s)
 
 // Sizes the rounds' training scratch for the resident shared sessions, within
 // what they leave of the budget: a session that needs the room gets it back.
+// Rounds run with whatever there is.
 void size_lanes(npm_server *s)
 {
-    std::lock_guard<std::mutex> ll(s->lanes_mu);
-    std::vector<const npm_ctx *> nets;
-    int64_t left;
-    {
-        std::lock_guard<std::mutex> lk(s->mu);
-        left = s->cfg.budget_bytes - s->bytes_in_use;
-        for (const Session &se : s->sessions)
-            if (se.alive && se.shared) nets.push_back(se.ctx);
+    int dev = s->device;
+    (void)hipGetDevice(&dev);
+    if (dev != s->device && hipSetDevice(s->device) != hipSuccess) return;
+    try {
+        std::lock_guard<std::mutex> ll(s->lanes_mu);
+        std::vector<Net> nets;      // copies: a session may go once the lock does
+        int64_t left;
+        {
+            std::lock_guard<std::mutex> lk(s->mu);
+            left = s->cfg.budget_bytes - s->bytes_in_use;
+            for (const Session &se : s->sessions)
+                if (se.alive && se.shared) nets.push_back(se.ctx->net);
+        }
+        serve_lanes_size(&s->lanes, s->cfg.round_vertices, left, nets, s->stream);
+    } catch (...) {
     }
-    serve_lanes_size(&s->lanes, s->cfg.round_vertices, left, nets, s->stream);
+    if (dev != s->device) (void)hipSetDevice(dev);
 }
 
 }  // namespace

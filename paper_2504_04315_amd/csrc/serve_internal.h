@@ -54,7 +54,7 @@ void serve_lanes_free(ServeLanes *l);
 // is freed.  A device without room leaves it smaller, down to nothing.
 constexpr int64_t kMinLaneVertices = 2048;
 void serve_lanes_size(ServeLanes *l, int64_t vertices, int64_t bytes,
-                      const std::vector<const npm_ctx *> &nets, hipStream_t s);
+                      const std::vector<Net> &nets, hipStream_t s);
 hipError_t round_buffers_init(RoundBuffers *b);
 void round_buffers_free(RoundBuffers *b);
 // Whether the persistent kernels are instantiated for this network shape.

@@ -82,3 +82,49 @@ def test_training_within_the_budget(O, extra):
         srv.destroy_session(sid)
     srv.close()
     assert torch.cuda.mem_get_info()[0] - free >= need      # the scratch went with the sessions
+
+
+def test_sessions_come_and_go_while_others_train():
+    # each creation and destruction sizes the scratch anew, from its own thread,
+    # beside rounds that use it; the training session ends where its own steps do
+    import threading
+    import torch
+    net = replace(W.CFG5, seed=95)
+    srv = S.Server(budget_bytes=8 << 30, max_sessions=16, round_vertices=1 << 16)
+    sid = srv.create_session(B.make_config(net))
+    errors = []
+
+    def visitor(k):
+        try:
+            cfg = B.make_config(replace(W.CFG5, seed=96 + k))
+            _, args = _args(torch, 1500, 96 + k)
+            for _ in range(6):
+                other = srv.create_session(cfg)
+                srv.submit_train(other, *args)
+                srv.destroy_session(other)
+        except Exception as e:                              # noqa: BLE001
+            errors.append(e)
+
+    threads = [threading.Thread(target=visitor, args=(k,)) for k in range(4)]
+    b, args = _args(torch, 20011, 95)
+    torch.cuda.synchronize()
+    for t in threads:
+        t.start()
+    for _ in range(8):
+        srv.wait(srv.submit_train(sid, *args))
+    for t in threads:
+        t.join()
+    assert not errors
+    assert srv.stats().sessions == 1
+    own = B.NPM(B.make_config(net))
+    for _ in range(8):
+        own.train_step(*args)
+    torch.cuda.synchronize()
+    # eight steps whose gradients are sums in another order: Adam moves a weight by
+    # its gradient's sign at first, so those at rounding level may differ altogether
+    # and the vector as a whole is compared, at BF16's few bits over the eight
+    m_own = own.get_state(B.STATE_ADAM_M).astype(np.float64)
+    m_srv = srv.session_state(sid, own.n_params, B.STATE_ADAM_M).astype(np.float64)
+    assert np.linalg.norm(m_srv - m_own) <= 2e-2 * np.linalg.norm(m_own)
+    own.close()
+    srv.close()
