@@ -507,6 +507,10 @@ def main():
     if "train_encode" in kt:
         work["train_encode"] = dict(bytes=16 + GATHER_B + feat_b, flops=0)
         work["fused_backward"] = dict(bytes=32 + feat_b + 32 * 4, flops=3 * MLP_F)
+        if args.precision == "fp32":
+            # the forward pass in FP32 matrix instructions, the backward pass's
+            # products as six BF16 ones each
+            work["fused_backward"]["units"] = {"f32": MLP_F, "bf16": 6 * 2 * MLP_F}
     if "bin_reduce" in kt:
         work.update(BIN_WORK)
         work["bin_reduce"] = dict(bytes=BIN_ITEMS_B + 2 * L_BINNED * T_HASH * 2 * 4 / n, flops=0)
@@ -530,7 +534,17 @@ def main():
     dom = max(known, key=lambda k: kt[k][1])
     r = rows[dom]
     dtype = args.precision if args.precision == "bf16" else "f32"
-    peak_tf = PEAK_TFLOPS[dtype]
+
+    def matrix_peak(rates):
+        """FLOP/s the dominant kernel would reach with its matrix units busy
+        throughout, at the given rates: its FLOPs over the time each unit's
+        share takes."""
+        units = work.get(dom, {}).get("units")
+        if not units:
+            return rates[dtype]
+        return work[dom]["flops"] / sum(f / rates[u] for u, f in units.items())
+
+    peak_tf = matrix_peak(PEAK_TFLOPS)
     if dom == "adam" or dom not in work or r["tflops"] / peak_tf < r["gbs"] / HBM_PEAK_GBS:
         bound, achieved, peak, unit = "hbm", r["gbs"], HBM_PEAK_GBS, "GB/s"
         per_launch = (work[dom]["bytes"] * n if dom in work else ADAM_BYTES_PER_PARAM * np_params)
@@ -538,7 +552,7 @@ def main():
         bound, achieved, peak, unit = "mfma", r["tflops"], peak_tf, "TFLOP/s"
         per_launch = work[dom]["flops"] * n
     tr = traffic.get("kernels", {}).get(dom)
-    roof = {"bound": bound, "achieved": round(achieved, 2), "peak": peak, "unit": unit,
+    roof = {"bound": bound, "achieved": round(achieved, 2), "peak": round(peak, 2), "unit": unit,
             "frac": round(achieved / peak, 4), "kernel": dom,
             "kernel_avg_ms": round(r["avg_ms"], 4), "algorithmic_per_launch": per_launch,
             # HBM bytes per launch from the FETCH_SIZE / WRITE_SIZE counters
@@ -549,7 +563,7 @@ def main():
         # the same kernel against what this device reaches with a plain kernel
         # of the bounding kind (matrix instructions alone, or the better of a
         # 2 GiB read stream and a 1 GiB copy)
-        ach = (peaks["mfma_bf16_tflops" if dtype == "bf16" else "mfma_f32_tflops"]
+        ach = (matrix_peak({"f32": peaks["mfma_f32_tflops"], "bf16": peaks["mfma_bf16_tflops"]})
                if bound == "mfma" else max(peaks["hbm_copy_gbs"], peaks["hbm_read_gbs"]))
         roof["achievable_peak"] = round(ach, 2)
         roof["frac_of_achievable"] = round(achieved / ach, 4)

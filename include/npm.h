@@ -93,14 +93,14 @@ enum { NPM_ORDER_AUTO = 0, NPM_ORDER_NONE = 1, NPM_ORDER_SPATIAL = 2 };
  * NPM_SCATTER_BINNED first bins the contributions of the hashed levels by
  * table slice and sums each slice in one block (in FP64, or in 64-bit fixed
  * point in the precision form; rounded once to FP32), then adds it to the
- * gradient.  Device scratch: 16 (1 + 2 F) n bytes
- * per binned level (80 n at F = 2), kept in the context.  In a spatially
+ * gradient.  Device scratch: 16 (2 + F) n bytes
+ * per binned level (64 n at F = 2), kept in the context.  In a spatially
  * ordered batch only the hashed levels with D_l >= 100 are binned; the others
  * keep the atomic path.  NPM_SCATTER_AUTO bins training batches of
  * 20000 vertices or more whose binned levels split into at least 128 slices
  * (16384 / F table entries each).  Both fall back to the atomic path when
  * the pass does not apply: no hashed level to bin, more than 2048 bins or
- * 1024 slices per level, or 2^32 items or more (n * 8 * binned levels).
+ * 1024 slices per level, or 2^32 items or more (n * 4 * binned levels).
  * Either way the gradient changes only in the order and width of its
  * floating-point sums.                                                     */
 enum { NPM_SCATTER_AUTO = 0, NPM_SCATTER_ATOMIC = 1, NPM_SCATTER_BINNED = 2 };

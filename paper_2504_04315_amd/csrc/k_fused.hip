@@ -449,8 +449,8 @@ hipError_t fused_backward(npm_ctx *ctx, int64_t n, const float *pos, const float
         // The chunked scatter and the weight-gradient sum write other parts
         // of the gradient than the binned scatter and read only the per-tile
         // dG: with bins they run on the side stream, beside the binned passes
-        // (which leave CUs idle in their scan and in the reduce's last wave of
-        // blocks), and the caller's stream waits for both.
+        // (whose blocks wait for memory and whose reduce ends in a partly filled
+        // wave of blocks), and the caller's stream waits for both.
         hipStream_t s2 = s;
         if (bins) {
             s2 = ctx->side;

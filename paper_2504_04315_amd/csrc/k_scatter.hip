@@ -303,8 +303,6 @@ k_scatter_chunk(GridDesc g, int64_t n, const float *__restrict__ pos, const uint
                 }
             }
         }
-        // groups of 8 lanes whose runs all ended in one cell share its sums,
-        // a lane per corner; the other lanes add their eight corners
         // neighbouring lanes whose runs ended in one cell merge their sums (8
         // lanes at most), and what is left goes to the lines
         merge_lanes<1, 8 * F, Sum>(cur, a, lane);

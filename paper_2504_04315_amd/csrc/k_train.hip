@@ -38,12 +38,13 @@
 // the end.
 //
 // Measured against the kernel that gathers (k_fused.hip), this one with its
-// encode: 2^20 vertices on the 16-level hash grid FP32 1,075 -> 248 + 636 us,
-// BF16 585 -> 198 + 240; NPM-product BF16, 300,001 vertices, 247 -> 79 + 113;
-// 8-level dense grid FP32, 2^18 vertices, 179 -> 20 + 137.  What bounds it now:
-// FP32 form, FP32 matrix 12.3k and vector 17k of 45k cycles a tile, the rest
-// BF16 products that a single wave does not overlap; precision form, vector
-// instructions (13k of 17k cycles).
+// encode: 2^20 vertices on the 16-level hash grid FP32 1,075 -> 248 + 671 us,
+// BF16 585 -> 198 + 250; NPM-product BF16, 300,001 vertices, 247 -> 83 + 118;
+// 8-level dense grid FP32, 2^18 vertices, 179 -> 21 + 129.  What bounds it now,
+// by counters at 2^20 vertices: FP32 form, 49k cycles a tile, the matrix unit
+// busy for half of them (FP32 products 12.3k, BF16 12k) and vector instructions
+// issuing for 42 %, which a single wave overlaps little; precision form, 18k
+// cycles, vector instructions for 62 %.
 #include <type_traits>
 
 #include "fused_launch.h"

@@ -261,11 +261,12 @@ constexpr int64_t kBinMinBatch = 20000;
 // 400,001 937 / 536, 1,000,001 2207 / 1753.
 constexpr int kBinMinBins = 128;
 // In a spatially ordered batch the hashed levels with D_l below this share
-// enough lines to stay with the chunked scatter.  Training step of the
-// 16-level production grid with the line at 100 / 140 / 180 / 250: 2^20
-// vertices FP32 1.68 / 1.61 / 1.63 / 1.66 ms, precision form 1.18 / 1.15 /
-// 1.18 / 1.19; 300,001 vertices 545 / 564 / 580 / 622 us; 100,003 vertices 470
-// / 473 / 484 / 499: sparser batches share fewer lines.
+// enough lines to stay with the chunked scatter.  One line for every batch size
+// lies where the sparser batches, which share fewer lines, want it: training
+// step of the 16-level production grid with the line at 100 / 140 / 180 / 250,
+// 100,003 vertices 470 / 473 / 484 / 499 us, 300,001 545 / 564 / 580 / 622; at
+// 2^20 140 would be the better one by 3 to 4 % (FP32 1.68 / 1.61 / 1.63 / 1.66
+// ms, precision form 1.18 / 1.15 / 1.18 / 1.19).
 constexpr int kBinMinResOrdered = 100;
 struct BinDesc {
     int32_t nb;                        // binned levels

@@ -631,7 +631,7 @@ static bool use_bins(const npm_ctx *ctx, int64_t n, bool ordered, BinDesc *b)
     if (ctx->net.cfg.exec_mode != NPM_EXEC_FUSED || mode == NPM_SCATTER_ATOMIC) return false;
     if (mode == NPM_SCATTER_AUTO && n < kBinMinBatch) return false;
     if (!bin_plan(ctx->net, n, ordered, b)) return false;
-    // a reduce of fewer blocks than compute units leaves most of the chip idle
+    // (kBinMinBins: few slices leave the reduce, a block each, too few blocks)
     return mode == NPM_SCATTER_BINNED || b->nbins >= kBinMinBins;
 }
 
